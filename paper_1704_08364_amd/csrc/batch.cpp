@@ -52,8 +52,8 @@ struct SizeClass {
     size_t polar_off = 0, dc_off = 0, grid_off = 0, mass_off = 0;
     // device arrays (inside the batch's table block): V per slice, work lists
     int* d_V = nullptr;
-    int* d_ang_off = nullptr;      // slice i's directions at d_ang + d_ang_off[i]
-    const double2* d_ang = nullptr;
+    int* d_ang_off = nullptr;      // slice i's directions at d_dir + d_ang_off[i]
+    const float4* d_dir = nullptr;
     int2* d_items[kStages] = {};
     int n_items[kStages] = {};
     int row_tiles = 1;         // row tiles per item of the row stage (tuned)
@@ -178,9 +178,10 @@ hipError_t launch_regular(const bst_batch_s* b, const SizeClass& c, void* ws, hi
     ga.uniform = p.uniform ? 1 : 0;
     ga.batch = batch;
     ga.slices_per_block = p.gather_slices;
-    ga.rscale = p.rscale;
+    bst::set_radius_scale(ga, p.rscale);
     ga.vpi_f = (float)p.vpi;
     ga.ang = p.ang;
+    ga.dir = p.dir;
     ga.dc_scale = p.dc_scale;
     if (p.tent) {
         float2* patch = reinterpret_cast<float2*>(w + L.tent_off);
@@ -241,10 +242,10 @@ hipError_t launch_class(const bst_batch_s* b, const SizeClass& c, void* ws, hipS
     ga.uniform = 1;
     ga.batch = batch;
     ga.slices_per_block = 1;
-    ga.rscale = p.rscale;
+    bst::set_radius_scale(ga, p.rscale);
     ga.dc_rule = p.dc_scale * (float)p.V;  // the plan's per-projection factor times its V
     ga.Vs = c.d_V;
-    ga.ang = c.d_ang;
+    ga.dir = c.d_dir;
     ga.ang_off = c.d_ang_off;
     ga.items = c.d_items[1];
     ga.n_items = c.n_items[1];
@@ -373,8 +374,8 @@ bst_status bst_batch_create(const bst_params* base, int32_t count, const int32_t
     }
     b->ws_total = off;
     // one device block: per class its V list, the offsets of its slices'
-    // direction tables, the tables ((cos, sin) of j pi / V_i, in FP64 as for
-    // a plan), then its three work lists
+    // direction tables, the tables (j pi / V_i, formed in FP64 as for a plan),
+    // then its three work lists
     auto up16 = [](size_t x) { return (x + 15) / 16 * 16; };
     size_t tbytes = 0;
     std::vector<size_t> v_off(b->classes.size()), a_off(b->classes.size()), d_off(b->classes.size()),
@@ -392,7 +393,7 @@ bst_status bst_batch_create(const bst_params* base, int32_t count, const int32_t
             release(b);
             return BST_E_BATCH;
         }
-        tbytes += dirs * sizeof(double2);
+        tbytes += dirs * sizeof(float4);
         for (int s = 0; s < kStages; ++s) {
             i_off[k * kStages + s] = tbytes;
             tbytes += std::max<size_t>(items[k * kStages + s].size(), 1) * sizeof(int2);
@@ -408,8 +409,8 @@ bst_status bst_batch_create(const bst_params* base, int32_t count, const int32_t
             std::memcpy(host.data() + a_off[k] + i * sizeof(int), &first, sizeof(int));
             for (int j = 0; j < V; ++j) {
                 const double th = (double)j * M_PI / (double)V;
-                const double2 d = make_double2(std::cos(th), std::sin(th));
-                std::memcpy(host.data() + d_off[k] + (size_t)(first + j) * sizeof(double2), &d, sizeof(double2));
+                const float4 d = bst::split_direction(std::cos(th), std::sin(th));
+                std::memcpy(host.data() + d_off[k] + (size_t)(first + j) * sizeof(float4), &d, sizeof(float4));
             }
             first += V;
         }
@@ -437,7 +438,7 @@ bst_status bst_batch_create(const bst_params* base, int32_t count, const int32_t
         SizeClass& c = b->classes[k];
         c.d_V = reinterpret_cast<int*>(tb + v_off[k]);
         c.d_ang_off = reinterpret_cast<int*>(tb + a_off[k]);
-        c.d_ang = reinterpret_cast<const double2*>(tb + d_off[k]);
+        c.d_dir = reinterpret_cast<const float4*>(tb + d_off[k]);
         for (int s = 0; s < kStages; ++s) c.d_items[s] = reinterpret_cast<int2*>(tb + i_off[k * kStages + s]);
     }
     b->d_sino_list = static_cast<const float**>(b->d_lists);

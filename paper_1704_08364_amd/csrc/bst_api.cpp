@@ -403,7 +403,11 @@ bst_status bst_plan(const bst_params* p, bst_plan_t* out) {
     }
     for (int j = 0; j < V; ++j) theta[j] = p->angles ? p->angles[j] : (double)j * M_PI / (double)V;
     const double ratio = d / pl->dt;
-    for (int j = 0; j < V; ++j) ang[j] = make_double2(std::cos(theta[j]), std::sin(theta[j]));
+    std::vector<float4> dir(V);
+    for (int j = 0; j < V; ++j) {
+        ang[j] = make_double2(std::cos(theta[j]), std::sin(theta[j]));
+        dir[j] = bst::split_direction(ang[j].x, ang[j].y);
+    }
     // 1 / (theta_{j+1} - theta_j) in the period-pi continuation (the last gap wraps to theta_0 + pi)
     for (int j = 0; j < V; ++j) {
         const double next = (j == V - 1) ? theta[0] + M_PI : theta[j + 1];
@@ -452,6 +456,7 @@ bst_status bst_plan(const bst_params* p, bst_plan_t* out) {
     const size_t o_s = off;     off = up(off + V * sizeof(double));
     const size_t o_w = off;     off = up(off + V * sizeof(float));
     const size_t o_ang = off;   off = up(off + V * sizeof(double2));
+    const size_t o_dir = off;   off = up(off + V * sizeof(float4));
     const size_t o_gap = off;   off = up(off + V * sizeof(float));
     const size_t o_prow = off;  off = up(off + V * sizeof(float));
     const size_t o_mphi = off;  off = up(off + n * sizeof(float));
@@ -468,6 +473,7 @@ bst_status bst_plan(const bst_params* p, bst_plan_t* out) {
     std::memcpy(host.data() + o_s, bf_s.data(), V * sizeof(double));
     std::memcpy(host.data() + o_w, bf_w.data(), V * sizeof(float));
     std::memcpy(host.data() + o_ang, ang.data(), V * sizeof(double2));
+    std::memcpy(host.data() + o_dir, dir.data(), V * sizeof(float4));
     std::memcpy(host.data() + o_gap, inv_gap.data(), V * sizeof(float));
     std::memcpy(host.data() + o_prow, proj_row.data(), V * sizeof(float));
     std::memcpy(host.data() + o_mphi, mono_phi.data(), n * sizeof(float));
@@ -576,6 +582,7 @@ bst_status bst_plan(const bst_params* p, bst_plan_t* out) {
     pl->bf_s = reinterpret_cast<double*>(base + o_s);
     pl->bf_w = reinterpret_cast<float*>(base + o_w);
     pl->ang = reinterpret_cast<double2*>(base + o_ang);
+    pl->dir = reinterpret_cast<float4*>(base + o_dir);
     pl->inv_gap = reinterpret_cast<float*>(base + o_gap);
     pl->proj_row = reinterpret_cast<float*>(base + o_prow);
     pl->mono_phi = reinterpret_cast<float*>(base + o_mphi);
@@ -698,9 +705,10 @@ bst_status run_backproject(bst_plan_t plan, const float* sino, float* img, int32
     ga.zero_slot = plan->M / 2 + plan->lead;
     ga.batch = batch;
     ga.slices_per_block = plan->gather_slices;
-    ga.rscale = plan->rscale;
+    bst::set_radius_scale(ga, plan->rscale);
     ga.vpi_f = (float)plan->vpi;
     ga.ang = plan->ang;
+    ga.dir = plan->dir;
     ga.inv_gap = plan->inv_gap;
     ga.uniform = plan->uniform ? 1 : 0;
     ga.dc_scale = plan->dc_scale;

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <rocprofiler-sdk-roctx/roctx.h>
 
+#include <cmath>
 #include <cstddef>
 #include <vector>
 
@@ -45,7 +46,8 @@ struct bst_plan_s {
     double* bf_c;        // [V]          cos(theta_j) * d/dt   (brute force)
     double* bf_s;        // [V]          sin(theta_j) * d/dt
     float* bf_w;         // [V]          w_j
-    double2* ang;        // [V]          (cos theta_j, sin theta_j), gather angle residuals
+    double2* ang;        // [V]          (cos theta_j, sin theta_j), non-uniform angles' residuals
+    float4* dir;         // [V]          the same as FP32 pairs (split_direction), uniform angles
     float* inv_gap;      // [V]          1 / (theta_{j+1} - theta_j), last gap to theta_0 + pi
     // adjoint (bst_project): transposed gather as CSR lists per polar sample
     bool adjoint;
@@ -127,6 +129,13 @@ struct PolarTiles {
         return (size_t)j * (size_t)S + (size_t)slot;
     }
 };
+// (cos, sin) of an angle for the gather's FP32 cross products: each as a high
+// part of 11 fractional bits, whose products with integers up to 2^12 are exact
+// in FP32, and the rest.
+inline float4 split_direction(double c, double s) {
+    const double ch = std::nearbyint(c * 2048.0) / 2048.0, sh = std::nearbyint(s * 2048.0) / 2048.0;
+    return make_float4((float)ch, (float)(c - ch), (float)sh, (float)(s - sh));
+}
 // slices interleaved in the tent rule's radius-major copy
 constexpr int kTentSlices = 8;
 // slices interleaved in the projector's Cartesian spectra (and summed together
@@ -205,10 +214,13 @@ struct GatherArgs {
     int zero_slot;           // first of the zero slots of a row; also the radius cut-off:
                              // points with r >= zero_slot read only zeros
     int batch, slices_per_block;
-    double rscale;
+    int rshift;              // log2(P_r / P_c): radial samples per Cartesian step
+    float rscale_f;          // 2^rshift
+    float rdown_f;           // 4^min(rshift, 0)
     float vpi_f;             // V / pi
     float dc_scale;
-    const double2* ang;      // [V] (cos theta_j, sin theta_j)
+    const double2* ang;      // [V] (cos theta_j, sin theta_j), non-uniform angles
+    const float4* dir;       // [V] the same as FP32 pairs (split_direction), uniform angles
     const float* inv_gap;    // [V] 1 / angle gap (non-uniform angles)
     int uniform;             // angles are j pi / V
     // tent angular rule (tent_cols != nullptr): wide points read their value
@@ -218,16 +230,22 @@ struct GatherArgs {
     int tent_w;
     // uneven batches: per-slice projection counts (nullptr: V for all; else
     // V is the layout's row count), the origin rule's factor (dc_scale =
-    // dc_rule / V of the slice), the slices' direction tables (slice s's
-    // (cos, sin) of j pi / V_s at ang + ang_off[s]; ang_off nullptr: formed
-    // with sincospi) and the work list of a persistent launch ((slice, column
-    // block) per item)
+    // dc_rule / V of the slice), the slices' direction tables (slice s's at
+    // dir + ang_off[s]) and the work list of a persistent launch ((slice,
+    // column block) per item)
     const int* Vs;
     const int* ang_off;
     float dc_rule;
     const int2* items;
     int n_items;
 };
+
+// the radius scale P_r / P_c, a power of two between 1/4 and 4
+inline void set_radius_scale(GatherArgs& a, double rscale) {
+    a.rshift = std::ilogb(rscale);
+    a.rscale_f = (float)rscale;
+    a.rdown_f = a.rshift < 0 ? (float)(rscale * rscale) : 1.f;
+}
 
 struct TentArgs {            // pre-gather of the wide points of the tent rule
     const float2* polar;     // groups of kPolarSlices slices (PolarTiles)
