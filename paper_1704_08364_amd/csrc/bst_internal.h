@@ -73,8 +73,8 @@ struct bst_plan_s {
     int2* tent_cols;     // [G/2]        (first slot of column a, B_a): rows |b| <= B_a are wide
     int4* tent_chunk;    // [chunks]     (slot, first tap j, last tap j, 0) in the continuation
     int* tent_coff;      // [tent_w + 1] chunk range of each slot
-    int gather_slices;   // slices per gather block (coordinates reused across them),
-                         // a multiple of kPolarSlices
+    int gather_slices;   // slices per gather block (coordinates reused across them), a
+                         // multiple of kPolarSlices; 0: chosen per launch
 };
 
 namespace bst {
@@ -213,7 +213,8 @@ struct GatherArgs {
     int GT;                  // grid tile-row width (columns)
     int zero_slot;           // first of the zero slots of a row; also the radius cut-off:
                              // points with r >= zero_slot read only zeros
-    int batch, slices_per_block;
+    int batch;
+    int slices_per_block;    // whole groups; 0: chosen by the launcher
     int rshift;              // log2(P_r / P_c): radial samples per Cartesian step
     float rscale_f;          // 2^rshift
     float rdown_f;           // 4^min(rshift, 0)

@@ -43,6 +43,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 namespace bst {
 
 __device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
@@ -175,12 +177,14 @@ __device__ __forceinline__ void dft(float2* v) {
 // w^((jj mod NS) * r) with w = exp(DIR 2 pi i / (NS R)), transforms, and
 // writes output r to position (jj / NS) * NS * R + (jj mod NS) + r * NS.
 // anc[k]: the twiddle anchor of butterfly k, already conjugated for DIR > 0
-template <int L, int DIR, int R, int NS, int E>
+// hook: the caller's work beside the butterflies (see fft)
+template <int L, int DIR, int R, int NS, int E, int PASS, class HOOK>
 __device__ __forceinline__ void stockham_pass(float2 (&v)[E], float2* lds, unsigned off, int j, const float2* anc,
-                                              int xm) {
+                                              int xm, HOOK& hook) {
     constexpr int T = L / E;
     constexpr int BPT = E / R;
     constexpr bool LAST = (NS * R == L);
+    hook(std::integral_constant<int, PASS>{});
 #pragma unroll
     for (int k = 0; k < BPT; ++k) {
         const int jj = j + k * T;
@@ -274,15 +278,24 @@ struct FftTwiddles {
     }
 };
 
-template <int LOGL, int DIR, int R, int NS, int E, int P>
+template <int LOGL, int DIR, int R, int NS, int E, int P, class HOOK>
 __device__ __forceinline__ void radix_passes(float2 (&v)[E], float2* lds, unsigned off, int j,
-                                             const FftTwiddles<LOGL, DIR, E>& tw, int xm) {
+                                             const FftTwiddles<LOGL, DIR, E>& tw, int xm, HOOK& hook) {
     constexpr int L = 1 << LOGL;
     if constexpr (NS < L) {
-        stockham_pass<L, DIR, R, NS, E>(v, lds, off, j, tw.w[P], xm);
-        radix_passes<LOGL, DIR, R, NS * R, E, (NS > 1 ? P + 1 : P)>(v, lds, off, j, tw, xm);
+        stockham_pass<L, DIR, R, NS, E, (NS > 1 ? P + 1 : P)>(v, lds, off, j, tw.w[P], xm, hook);
+        radix_passes<LOGL, DIR, R, NS * R, E, (NS > 1 ? P + 1 : P)>(v, lds, off, j, tw, xm, hook);
     }
 }
+
+// No work beside the butterflies.
+struct FftNoHook {
+    template <class POS>
+    __device__ __forceinline__ void operator()(POS) {}
+};
+// Passes of a transform.
+template <int LOGL, int DIR, int E>
+constexpr int fft_passes() { return FftTwiddles<LOGL, DIR, E>::NT + 1; }
 
 // Full transform of length 2^LOGL by L/E threads holding E (8, 16 or 32)
 // values each; passes are radix min(E, 16) after one smaller first pass when
@@ -290,18 +303,27 @@ __device__ __forceinline__ void radix_passes(float2 (&v)[E], float2* lds, unsign
 // the block's LDS array, and the transform's region of L float2 at byte `off`
 // (a multiple of 8 L; positions lds_swz<E>(i) ^ xm) must not be read by
 // anyone else meanwhile. Ends with a barrier if any LDS exchange happened.
-template <int LOGL, int DIR, int E = 16>
+// hook(integral_constant<int, i>) is called by every thread before the
+// butterflies of pass i: work of the caller that does not touch the region and
+// that the butterflies' arithmetic can overlap.
+template <int LOGL, int DIR, int E, class HOOK>
 __device__ __forceinline__ void fft(float2 (&v)[E], float2* lds, unsigned off, int j,
-                                    const FftTwiddles<LOGL, DIR, E>& tw, int xm) {
+                                    const FftTwiddles<LOGL, DIR, E>& tw, int xm, HOOK& hook) {
     static_assert(E == 8 || E == 16 || E == 32, "8, 16 or 32 values per thread");
     using TW = FftTwiddles<LOGL, DIR, E>;
     constexpr int L = 1 << LOGL;
     if constexpr (TW::REM != 0) {
-        stockham_pass<L, DIR, (1 << TW::REM), 1, E>(v, lds, off, j, tw.w[0], xm);
-        radix_passes<LOGL, DIR, TW::R, (1 << TW::REM), E, 0>(v, lds, off, j, tw, xm);
+        stockham_pass<L, DIR, (1 << TW::REM), 1, E, 0>(v, lds, off, j, tw.w[0], xm, hook);
+        radix_passes<LOGL, DIR, TW::R, (1 << TW::REM), E, 0>(v, lds, off, j, tw, xm, hook);
     } else {
-        radix_passes<LOGL, DIR, TW::R, 1, E, 0>(v, lds, off, j, tw, xm);
+        radix_passes<LOGL, DIR, TW::R, 1, E, 0>(v, lds, off, j, tw, xm, hook);
     }
+}
+template <int LOGL, int DIR, int E = 16>
+__device__ __forceinline__ void fft(float2 (&v)[E], float2* lds, unsigned off, int j,
+                                    const FftTwiddles<LOGL, DIR, E>& tw, int xm) {
+    FftNoHook none;
+    fft<LOGL, DIR, E>(v, lds, off, j, tw, xm, none);
 }
 
 // The same, reading the twiddle anchors from the table first.

@@ -17,13 +17,22 @@
 // points of N = 2048 with two columns per block: 7.9 distinct 128-byte lines
 // per wave and slice, against 9.9 for interleaved rows and 16.4 for one
 // slice per row). A block therefore gathers both slices of a group at once;
-// their column transforms run one after the other, each gathered column
-// waiting in its own LDS region. Cubic taps keep one slice per group in plain
-// rows (Q = 1), and uneven batches too (their slices differ in V).
+// their column transforms run one after the other. Cubic taps keep one slice
+// per group in plain rows (Q = 1), and uneven batches too (their slices differ
+// in V).
 //
-// Blocks have 1024 threads for transforms of 4096 points or more and 512
-// below, where two blocks share a compute unit and one block's transforms
-// overlap the other's polar reads (gather_threads).
+// A thread gathers the points its transform starts from, so gathered values
+// stay in its registers (16 points per thread at two waves per SIMD from G =
+// 2048 on, which takes one LDS exchange fewer than 8 points at four). The polar
+// reads (64 slices of 2048^2: 1.28 ms on their own, bound by the latency of L1
+// misses), the transforms (0.87 ms, vector ALU) and the grid stores (0.4 ms)
+// ran one after the other, 2.2 ms; a block that walks several groups now reads
+// the next group's points between the butterflies of the current one, a pair's
+// first slice waiting in LDS: 2.02 ms (cubic taps at P_c = 1: 1.28 -> 1.11).
+// Blocks of one group keep nothing in LDS but the transforms and overlap
+// through several blocks per compute unit: 8 slices of 256^2 42.8 -> 13.2 us,
+// 2 of 2048^2 89 -> 66, one of 256^2 16.7 -> 10.2 (the coordinates' part of
+// that below).
 //
 // Each thread keeps the interpolation coordinates of its E points in
 // three registers each and reuses them for every slice of its chunk. They
@@ -62,21 +71,20 @@
 
 namespace bst {
 
-// Threads per block of the gather kernel (the columns per block follow from
-// it): 1024 for transforms of 4096 points and more (two columns of 4096; two
-// 512-thread blocks of one column each per compute unit measured 14 % slower,
-// their footprints no longer shared), 512 below (two blocks per compute
-// unit, one transforming while the other gathers: 7-21 % faster at G = 1024
-// and 2048 than one 1024-thread block).
-#ifndef BST_GATHER_THREADS
-#define BST_GATHER_THREADS 0
-#endif
-constexpr int gather_threads(int G) { return BST_GATHER_THREADS ? BST_GATHER_THREADS : (G >= 4096 ? 1024 : 512); }
-
-// waves per SIMD the register allocation must leave room for
-#ifndef BST_GATHER_WAVES
-#define BST_GATHER_WAVES 4
-#endif
+// Points (transform values) per thread: 16 from G = 2048 on, at two waves per
+// SIMD, 8 below, at four. It fixes the transform's arithmetic, so it depends on
+// G alone: a slice's result is the same in every batch.
+constexpr int gather_points(int G) { return G >= 2048 ? 16 : 8; }
+// Threads per block (the columns per block follow). PIPE: blocks that walk
+// several groups, each group's gather overlapped with the previous one's
+// transforms (G >= 2048). The others overlap through several blocks per compute
+// unit. (256-thread blocks of one column at G = 4096 lose the shared lines: 2.57 ms
+// against 2.03 for 64 slices of 2048^2; 128-thread ones at G = 1024 and 2048
+// gather 1.1 to 1.3 times slower, 512-thread ones up to 1.3 times.)
+constexpr int gather_threads(int G, bool pipe) { return pipe && G >= 4096 ? 512 : (G <= 512 ? 128 : 256); }
+// arithmetic instructions between two polar reads of the overlapped gather
+// (64 slices of 2048^2: 2.17 ms with 8, 2.06 with 14, 2.04 with 20, 2.07 with 28)
+constexpr int kReadSpacing = 20;
 
 // Word 3 of a CDNA buffer resource for plain dword data (32-bit data format,
 // no swizzle, raw offsets).
@@ -99,26 +107,32 @@ __device__ __forceinline__ float4 load16(__amdgpu_buffer_rsrc_t r, unsigned off)
     return make_float4(__uint_as_float(q[0]), __uint_as_float(q[1]), __uint_as_float(q[2]), __uint_as_float(q[3]));
 }
 
-template <int LOGG, int QV = kPolarSlices, int CAPT = 0>
+template <int LOGG, int QV, int CAP, bool PIPE>
 struct GatherCfg {
     static constexpr int G = 1 << LOGG;
     static constexpr int Q = QV;                         // slices per polar group
-    static constexpr int E = 8;                          // points (values) per thread
+    static constexpr int E = gather_points(G);           // points (values) per thread
     static constexpr int T = G / E;
-    static constexpr int CAP = CAPT ? CAPT : gather_threads(G);
-    static constexpr int WAVES = BST_GATHER_WAVES;       // per SIMD, for the registers
-    static constexpr int MAXT = CAP > T ? CAP : T;
-    static constexpr int FL = 16384 / G;                 // LDS: two regions of about 70 KB
-    static constexpr int F1 = FL < G / 2 ? FL : G / 2;   // no more columns than exist
-    static constexpr int F2 = MAXT / T;
-    static constexpr int F = F1 < F2 ? F1 : F2;          // columns per block
+    static constexpr int WAVES = E == 16 ? 2 : 4;        // per SIMD, for the registers
+    static constexpr int F1 = CAP > T ? CAP / T : 1;     // columns per block:
+    static constexpr int F = F1 < G / 2 ? F1 : G / 2;    // no more than exist
     static constexpr int WG = F * T;
     // transform stride in LDS (float2; a power of two, the columns' lanes
     // interleaved and their positions told apart by region_xor)
     static constexpr int STRIDE = G;
     static constexpr int REGION = F * STRIDE;            // one slice's F transforms
-    static constexpr int NREG = Q < 2 ? Q : 2;           // LDS regions (parked slices)
+    static constexpr bool PARK = PIPE && Q == 2;         // a second region: a pair's parked slice
+    static constexpr int NREG = PARK ? 2 : 1;
 };
+
+// f(integral_constant<int, i>) for i = 0 .. N - 1
+template <int N, int I = 0, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<N, I + 1>(f);
+    }
+}
 
 template <int WG>
 __device__ float block_sum(float x, float* red) {
@@ -332,6 +346,30 @@ __device__ __forceinline__ void store_streaming(float2* p, float2 v) {
     __builtin_nontemporal_store(t, reinterpret_cast<f2v*>(p));
 }
 
+// Column `col`'s rows of one slice that survive the crop, those of points e <
+// KEEP and e >= E - KEEP, to the slice's grid D (8-row tiles [N/8][GT][8]).
+// From T = 8 on the rows of a thread differ by whole tiles: one 32-bit lane
+// offset (a slice has at most 2^27 bytes) against a base per point.
+template <int LOGG, int E, int KEEP>
+__device__ __forceinline__ void store_rows(const float2 (&v)[E], float2* D, const GatherArgs& a, int j, int col) {
+    constexpr int G = 1 << LOGG, T = G / E;
+    constexpr int N = G * 2 * KEEP / E;
+    [[maybe_unused]] const unsigned elems = (unsigned)N * (unsigned)a.GT;
+    const unsigned lane = (((unsigned)j >> 3) * (unsigned)a.GT + (unsigned)col) * 8u + ((unsigned)j & 7u);
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        if (e >= KEEP && e < E - KEEP) continue;
+        const int first = e * T + (e < KEEP ? N / 2 : N / 2 - G);  // row of thread 0
+        if constexpr (T >= 8) {
+            const unsigned base = (unsigned)(first / 8) * (unsigned)a.GT * 8u;
+            store_streaming(D + base + BST_IDX(lane, elems - base, 2), v[e]);
+        } else {
+            const unsigned p = (unsigned)(first + j);
+            store_streaming(D + BST_IDX(((p >> 3) * (unsigned)a.GT + (unsigned)col) * 8u + (p & 7u), elems, 2), v[e]);
+        }
+    }
+}
+
 // Keys cubic convolution (a = -1/2) over samples m0-1 .. m0+2 at fraction g:
 // the Catmull-Rom weights.
 __device__ __forceinline__ float2 keys4(float2 sm, float2 s0, float2 s1, float2 s2, float g) {
@@ -383,13 +421,13 @@ __device__ __forceinline__ void radial_row(const float4 (&q)[TAPS * Q / 2], floa
 // One block's work: columns lblock * F .. + F - 1 for the slices
 // [s_begin, s_end) (whole groups of Q). The slices share one angle set: the
 // plan's, or (per-slice counts) that of slice s_begin.
-template <int LOGG, int TAPS, bool NU, bool TENT, int Q, int CAPT = 0>
+template <int LOGG, int TAPS, bool NU, bool TENT, int Q, int CAP, bool PIPE>
 __device__ __forceinline__ void gather_body(const GatherArgs& a, int lblock, int s_begin, int s_end) {
-    using C = GatherCfg<LOGG, Q, CAPT>;
+    using C = GatherCfg<LOGG, Q, CAP, PIPE>;
     constexpr int G = C::G, T = C::T, F = C::F, E = C::E;
     constexpr unsigned kSampleBytes = Q * sizeof(float2);
     constexpr bool TILED = Q == 2 && TAPS == 2;  // the 2 x 4 x 2 tiles of PolarTiles
-    __shared__ float2 lds[C::NREG * C::REGION];  // one region per parked slice
+    __shared__ float2 lds[C::NREG * C::REGION];
     __shared__ float red[(C::WG + 63) / 64];
     const int fid = threadIdx.x % F;
     const int j = threadIdx.x / F;
@@ -462,7 +500,6 @@ __device__ __forceinline__ void gather_body(const GatherArgs& a, int lblock, int
     const unsigned zcode = sample_code<TILED>(a, 0, a.zero_slot);  // a zero sample
     const unsigned zoff = (zcode & kSampleMask) * kSampleBytes;
 
-    const int half_n = a.N >> 1;
     const PolarTiles lay{Q, a.V, a.S};
     const unsigned group_bytes = (unsigned)(lay.group_elems() * sizeof(float2));
     const unsigned row_bytes = (unsigned)a.S * kSampleBytes;
@@ -472,163 +509,280 @@ __device__ __forceinline__ void gather_body(const GatherArgs& a, int lblock, int
     const unsigned tile_row_bytes = (unsigned)lay.tiles_per_row() * 128u;
     const unsigned tile_next = tile_row_bytes - 64u;
     const unsigned tile_wrap = 0u - (unsigned)((V - 1) >> 1) * tile_row_bytes - (unsigned)((V - 1) & 1) * 64u;
-    // column fid's LDS regions: slice 0 of a group at byte off0, slice 1 at off1
-    const unsigned off0 = (unsigned)(fid * C::STRIDE) * 8u;
-    const unsigned off1 = off0 + (unsigned)((C::NREG - 1) * C::REGION) * 8u;
+    const unsigned off = (unsigned)(fid * C::STRIDE) * 8u;  // column fid's transform region
     const int xm = region_xor<LOGG, F>(fid);
-    for (int s0 = s_begin; s0 < s_end; s0 += Q) {
-        const int nq = min(Q, s_end - s0);  // slices of this group in the batch
-        // Re-derive the lane's row index each group: otherwise every address
-        // that depends on it (LDS passes, grid stores) is hoisted out of the
-        // loop and held in registers, which spills.
-        int jv = j;
-        asm volatile("" : "+v"(jv));
-        const unsigned pj0 = lds_byte(off0, lds_swz<E>(jv), xm);  // the thread's first point
-        const unsigned pj1 = lds_byte(off1, lds_swz<E>(jv), xm);
-        const __amdgpu_buffer_rsrc_t P = polar_rsrc(a.polar + (size_t)(s0 / Q) * lay.group_elems(), group_bytes);
-        float dcv[Q];
+    float2* const park = lds + (C::NREG - 1) * C::REGION + threadIdx.x;  // the thread's own slots, WG apart
+    const int keep = (a.N * E) / (2 * G);  // E/2, E/4 or E/8 for P_c = 1, 2, 4 (store_rows)
+
+    // The group being gathered: its polar block, its first slice, its origin values.
+    __amdgpu_buffer_rsrc_t P = polar_rsrc(a.polar + (size_t)(s_begin / Q) * lay.group_elems(), group_bytes);
+    int sg = s_begin;
+    float dcv[Q];
+    auto open_group = [&](int s0) {
+        sg = s0;
+        P = polar_rsrc(a.polar + (size_t)(s0 / Q) * lay.group_elems(), group_bytes);
         if (lblock == 0) {
 #pragma unroll
             for (int k = 0; k < Q; ++k) {
+                // the same order of additions in every block size
+                constexpr int W = C::WG < 256 ? C::WG : 256;
                 float acc = 0.f;
-                if (k < nq)
-                    for (int i = threadIdx.x; i < V; i += C::WG) acc += a.dc[(size_t)(s0 + k) * a.V + i];
+                if (s0 + k < s_end && threadIdx.x < W)
+                    for (int i = threadIdx.x; i < V; i += W) acc += a.dc[(size_t)(s0 + k) * a.V + i];
                 dcv[k] = block_sum<C::WG>(acc, red) * dc_scale;
             }
         }
-        // gather: each slice of the group waits in its own LDS region. One
-        // point at a time: its four 16-byte reads mostly share one or two cache
-        // lines, and with fewer reads in flight the lines are still in L1 when
-        // the next point of a neighbouring lane needs them (two points at a time
-        // measured 2 % slower with the tiled layout, four 30 % slower, spilling).
+    };
+    // The polar reads of point e, then its values. PIPE: slice 0 of a pair into
+    // the thread's parking slot, the other one into nxt[0]; else nxt[slice].
+    // points in flight together: those of one pass
+    constexpr int D = (E + Q * fft_passes<LOGG, +1, E>() - 1) / (Q * fft_passes<LOGG, +1, E>());
+    float4 qa[D][TAPS * Q / 2], qb[D][TAPS * Q / 2];
+    float2 nxt[PIPE ? 1 : Q][E];
+    // (the stencils are made opaque at each use: otherwise every point's four
+    // addresses and both signed weights are formed once and spill)
+    auto issue = [&](auto pe) {
+        constexpr int e = decltype(pe)::value;
+        Stencil& st = pt[e];
+        asm volatile("" : "+v"(st.o0), "+v"(st.g));
+        const bool wrap = __float_as_uint(st.g) >> 31;
+        const bool zero = TENT && ((wide >> e) & 1u);
+        if constexpr (TILED) {
+            // (j0, m0) and (j0, m0 + 1): 16 bytes apart, or 80 across a tile edge
+            const unsigned code = zero ? zcode : st.o0;
+            const unsigned oa = BST_IDX((code & kSampleMask) * 16u, group_bytes - 15u, 0);
+            const unsigned ob = BST_IDX(oa + (((code >> 29) & 1u) ? 80u : 16u), group_bytes - 15u, 0);
+            const unsigned d1 = wrap ? tile_wrap : (((code >> 30) & 1u) ? tile_next : 64u);
+            qa[e % D][0] = load16(P, oa);
+            qa[e % D][1] = load16(P, ob);
+            qb[e % D][0] = load16(P, BST_IDX(oa + d1, group_bytes - 15u, 0));
+            qb[e % D][1] = load16(P, BST_IDX(ob + d1, group_bytes - 15u, 0));
+        } else {
+            [[maybe_unused]] constexpr unsigned kLast = TAPS * kSampleBytes - 1u;  // bytes read past the offset
+            const unsigned o0 = BST_IDX(zero ? zoff : st.o0 * kSampleBytes, group_bytes - kLast, 0);
+            const unsigned o1 = BST_IDX(o0 + (wrap ? wrap_bytes : row_bytes), group_bytes - kLast, 0);
+            load_row<TAPS, Q>(P, o0, qa[e % D]);
+            load_row<TAPS, Q>(P, o1, qb[e % D]);
+        }
+    };
+    auto take = [&](auto pe) {
+        constexpr int e = decltype(pe)::value;
+        Stencil& st = pt[e];
+        asm volatile("" : "+v"(st.g), "+v"(st.w1));
+        const float g = fabsf(st.g);
+        float2 u0[Q], u1[Q], val[Q];
+        radial_row<TAPS, Q>(qa[e % D], g, u0);
+        radial_row<TAPS, Q>(qb[e % D], g, u1);
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
-            const Stencil& st = pt[e];
-            const bool wrap = __float_as_uint(st.g) >> 31;
-            const bool zero = TENT && ((wide >> e) & 1u);
-            float4 qa[TAPS * Q / 2], qb[TAPS * Q / 2];
-            if constexpr (TILED) {
-                // (j0, m0) and (j0, m0 + 1): 16 bytes apart, or 80 across a tile edge
-                const unsigned code = zero ? zcode : st.o0;
-                const unsigned oa = BST_IDX((code & kSampleMask) * 16u, group_bytes - 15u, 0);
-                const unsigned ob = BST_IDX(oa + (((code >> 29) & 1u) ? 80u : 16u), group_bytes - 15u, 0);
-                const unsigned d1 = wrap ? tile_wrap : (((code >> 30) & 1u) ? tile_next : 64u);
-                qa[0] = load16(P, oa);
-                qa[1] = load16(P, ob);
-                qb[0] = load16(P, BST_IDX(oa + d1, group_bytes - 15u, 0));
-                qb[1] = load16(P, BST_IDX(ob + d1, group_bytes - 15u, 0));
-            } else {
-                [[maybe_unused]] constexpr unsigned kLast = TAPS * kSampleBytes - 1u;  // bytes read past the offset
-                const unsigned o0 = BST_IDX(zero ? zoff : st.o0 * kSampleBytes, group_bytes - kLast, 0);
-                const unsigned o1 = BST_IDX(o0 + (wrap ? wrap_bytes : row_bytes), group_bytes - kLast, 0);
-                load_row<TAPS, Q>(P, o0, qa);
-                load_row<TAPS, Q>(P, o1, qb);
-            }
-            const float g = fabsf(st.g);
-            float2 u0[Q], u1[Q], val[Q];
-            radial_row<TAPS, Q>(qa, g, u0);
-            radial_row<TAPS, Q>(qb, g, u1);
+        for (int k = 0; k < Q; ++k) val[k] = angular(u0[k], u1[k], st.w1, lower_j0<NU>(flips, e, 2 * e >= E));
+        if constexpr (TENT) {
+            // wide points: the value pre-gathered over their tent of angles
+            if ((wide >> e) & 1u) {
 #pragma unroll
-            for (int k = 0; k < Q; ++k) val[k] = angular(u0[k], u1[k], st.w1, lower_j0<NU>(flips, e, 2 * e >= E));
-            if constexpr (TENT) {
-                // wide points: the value pre-gathered over their tent of angles
-                if ((wide >> e) & 1u) {
-#pragma unroll
-                    for (int k = 0; k < Q; ++k) {
-                        const int sk = min(s0 + k, a.batch - 1);
-                        val[k] = a.patch[(size_t)sk * a.tent_w + BST_IDX(st.o0, (unsigned)a.tent_w, 1)];
-                    }
+                for (int k = 0; k < Q; ++k) {
+                    const int sk = min(sg + k, a.batch - 1);
+                    val[k] = a.patch[(size_t)sk * a.tent_w + BST_IDX(st.o0, (unsigned)a.tent_w, 1)];
                 }
             }
-            // origin: column 0, row 0 is thread j = 0's first point
-            if (e == 0 && col == 0 && jv == 0) {
+        }
+        // origin: column 0, row 0 is thread j = 0's first point
+        if constexpr (e == 0) {
+            if (col == 0 && j == 0) {
 #pragma unroll
                 for (int k = 0; k < Q; ++k) val[k] = make_float2(dcv[k], 0.f);
             }
-            lds_at(lds, pj0 ^ swz_bytes<E>(e * T)) = val[0];
-            if constexpr (Q > 1) lds_at(lds, pj1 ^ swz_bytes<E>(e * T)) = val[1];
-            asm volatile("" ::: "memory");
         }
-        __syncthreads();
-
-        // One transform per iteration, the loop kept rolled: unrolled, the
-        // transforms share address arithmetic that then stays live across
-        // all of them and spills. Each slice comes from its LDS region.
-#pragma unroll 1
-        for (int k = 0; k < nq; ++k) {
-            int jk = jv;
-            asm volatile("" : "+v"(jk));
-            const unsigned offk = (k & 1) ? off1 : off0;
-            const unsigned pk = lds_byte(offk, lds_swz<E>(jk), xm);
-            float2 v[E];
+        // formed here: left to itself the compiler keeps the reads' registers
+        // until the value is used, a whole transform later
+        if constexpr (PIPE) {
+            if constexpr (Q == 2) park[e * C::WG] = val[0];
+            nxt[0][e] = val[Q - 1];
+            asm volatile("" : "+v"(nxt[0][e].x), "+v"(nxt[0][e].y));
+        } else {
 #pragma unroll
-            for (int e = 0; e < E; ++e) v[e] = lds_at(lds, pk ^ swz_bytes<E>(e * T));
-            __syncthreads();  // every lane has its inputs before the first pass writes
+            for (int k = 0; k < Q; ++k) {
+                nxt[k][e] = val[k];
+                asm volatile("" : "+v"(nxt[k][e].x), "+v"(nxt[k][e].y));
+            }
+        }
+    };
+    // The next group's points are spread over the passes of this group's
+    // transforms: pass r takes the points issued in pass r - 1 and issues its
+    // own, their reads spaced out between the pass's butterflies (a burst of
+    // reads from all waves at once would stall them in issue).
+    constexpr int PASSES = Q * fft_passes<LOGG, +1, E>();
+    constexpr int kReads = TAPS * Q;  // read instructions of a point
+    auto first_of = [](int r) constexpr { return r * E / PASSES; };
+    auto take_pass = [&](auto pr) {
+        constexpr int lo = first_of(decltype(pr)::value), hi = first_of(decltype(pr)::value + 1);
+        static_for<hi - lo>([&](auto pi) { take(std::integral_constant<int, lo + decltype(pi)::value>{}); });
+    };
+    auto issue_pass = [&](auto pr) {
+        constexpr int lo = first_of(decltype(pr)::value), hi = first_of(decltype(pr)::value + 1);
+        static_for<hi - lo>([&](auto pi) { issue(std::integral_constant<int, lo + decltype(pi)::value>{}); });
+        static_for<(hi - lo) * kReads>([&](auto) {
+            __builtin_amdgcn_sched_group_barrier(0x0020, 1, 0);   // one vector memory read
+            __builtin_amdgcn_sched_group_barrier(0x0002, kReadSpacing, 0);  // arithmetic
+        });
+    };
+    auto step = [&](auto pr) {
+        constexpr int r = decltype(pr)::value;
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (r > 0) take_pass(std::integral_constant<int, r - 1>{});
+        __builtin_amdgcn_sched_barrier(0);
+        issue_pass(pr);
+    };
+
+    // a group gathered on its own, D points' reads in flight
+    auto gather_group = [&]() {
+        static_for<D>([&](auto pe) { issue(pe); });
+        static_for<E>([&](auto pe) {
+            constexpr int e = decltype(pe)::value;
+            take(pe);
+            if constexpr (e + D < E) issue(std::integral_constant<int, e + D>{});
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    // One group's transforms, with (MORE) the next group's gather between their
+    // exchanges. nq: the slices of the group in the batch.
+    auto transforms = [&](auto pmore, int s0, int nq) {
+        constexpr bool MORE = decltype(pmore)::value;
+        float2 cur[Q][E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            if constexpr (C::PARK) cur[0][e] = park[e * C::WG];
+            if constexpr (PIPE) {
+                cur[Q - 1][e] = nxt[0][e];
+            } else {
+#pragma unroll
+                for (int k = 0; k < Q; ++k) cur[k][e] = nxt[k][e];
+            }
+        }
+        if constexpr (MORE) open_group(s0 + Q);
+        static_for<Q>([&](auto pk) {
+            constexpr int k = decltype(pk)::value;
+            if (!MORE && k >= nq) return;
+            // Re-derive the lane's row index for each transform: otherwise every
+            // address that depends on it (LDS passes, grid stores) is computed
+            // once and held in registers, which spills.
+            int jk = j;
+            asm volatile("" : "+v"(jk));
             FftTwiddles<LOGG, +1, E> twl = tw;
             twl.pin();
-            fft<LOGG, +1, E>(v, lds, offk, jk, twl, xm);
+            auto hook = [&](auto ph) {
+                if constexpr (MORE) step(std::integral_constant<int, k * (PASSES / Q) + decltype(ph)::value>{});
+            };
+            fft<LOGG, +1, E>(cur[k], lds, off, jk, twl, xm, hook);
             if (live) {
                 float2* D = a.grid + (size_t)(s0 + k) * a.N * a.GT;
-#pragma unroll
-                for (int e = 0; e < E; ++e) {
-                    const int y = jk + e * T;
-                    const int p = (y + half_n) & (G - 1);
-                    if (p < a.N)
-                        store_streaming(&D[BST_IDX(((size_t)(p >> 3) * a.GT + col) * 8 + (p & 7),
-                                                   (size_t)a.N * a.GT, 2)], v[e]);
-                }
+                if (keep == E / 2) store_rows<LOGG, E, E / 2>(cur[k], D, a, jk, col);
+                else if (keep == E / 4) store_rows<LOGG, E, E / 4>(cur[k], D, a, jk, col);
+                else store_rows<LOGG, E, E / 8>(cur[k], D, a, jk, col);
             }
+        });
+        if constexpr (MORE) take_pass(std::integral_constant<int, PASSES - 1>{});
+    };
+    if constexpr (PIPE) {
+        // the first group has nothing to hide its reads behind
+        open_group(s_begin);
+        gather_group();
+        int s0 = s_begin;
+#pragma unroll 1
+        for (; s0 + Q < s_end; s0 += Q) transforms(std::true_type{}, s0, Q);
+        transforms(std::false_type{}, s0, s_end - s0);
+    } else {
+#pragma unroll 1
+        for (int s0 = s_begin; s0 < s_end; s0 += Q) {
+            open_group(s0);
+            gather_group();
+            transforms(std::false_type{}, s0, s_end - s0);
         }
     }
 }
 
-template <int LOGG, int TAPS, bool NU, bool TENT>
-__global__ void __launch_bounds__((GatherCfg<LOGG, polar_group(TAPS)>::WG))
-__attribute__((amdgpu_waves_per_eu(GatherCfg<LOGG, polar_group(TAPS)>::WAVES, 8))) k_gather_colifft(GatherArgs a) {
+template <int LOGG, int TAPS, bool PIPE>
+using GatherKernelCfg = GatherCfg<LOGG, polar_group(TAPS), gather_threads(1 << LOGG, PIPE), PIPE>;
+
+template <int LOGG, int TAPS, bool NU, bool TENT, bool PIPE>
+__global__ void __launch_bounds__((GatherKernelCfg<LOGG, TAPS, PIPE>::WG))
+__attribute__((amdgpu_waves_per_eu(GatherKernelCfg<LOGG, TAPS, PIPE>::WAVES, 8))) k_gather_colifft(GatherArgs a) {
     const int s_begin = blockIdx.y * a.slices_per_block;  // a multiple of Q
-    gather_body<LOGG, TAPS, NU, TENT, polar_group(TAPS)>(a, xcd_contiguous(blockIdx.x, gridDim.x), s_begin,
-                                                         min(a.batch, s_begin + a.slices_per_block));
+    gather_body<LOGG, TAPS, NU, TENT, polar_group(TAPS), gather_threads(1 << LOGG, PIPE), PIPE>(
+        a, xcd_contiguous(blockIdx.x, gridDim.x), s_begin, min(a.batch, s_begin + a.slices_per_block));
 }
 
 // Persistent launch of uneven batches (one slice per group, uniform angles):
 // every block walks the work list (slice, column block) in steps of the grid,
 // the blocks of one XCD taking contiguous items (the neighbouring columns of
-// one slice, which read the same polar lines). Blocks of 1024 threads at
-// every length: the classes' persistent kernels run side by side, and
-// 512-thread blocks measured slower there.
-constexpr int kItemsThreads = 1024;
+// one slice, which read the same polar lines). Blocks of 512 threads at every
+// length (96 uneven sinograms: 3.5 ms, with 256 threads 4.7, with 1024 5.2).
+constexpr int kItemsThreads = 512;
+template <int LOGG>
+using ItemsCfg = GatherCfg<LOGG, 1, kItemsThreads, false>;
 template <int LOGG, int TAPS>
-__global__ void __launch_bounds__((GatherCfg<LOGG, 1, kItemsThreads>::WG))
-__attribute__((amdgpu_waves_per_eu(GatherCfg<LOGG, 1, kItemsThreads>::WAVES, 8))) k_gather_items(GatherArgs a) {
+__global__ void __launch_bounds__((ItemsCfg<LOGG>::WG))
+__attribute__((amdgpu_waves_per_eu(ItemsCfg<LOGG>::WAVES, 8))) k_gather_items(GatherArgs a) {
     const int local = xcd_contiguous(blockIdx.x, gridDim.x);
     for (int base = 0; base < a.n_items; base += gridDim.x) {
         const int it = base + local;
         if (it >= a.n_items) break;
         const int2 w = a.items[it];
         __syncthreads();  // the previous item's LDS reads are done
-        gather_body<LOGG, TAPS, false, false, 1, kItemsThreads>(a, w.y, w.x, w.x + 1);
+        gather_body<LOGG, TAPS, false, false, 1, kItemsThreads, false>(a, w.y, w.x, w.x + 1);
     }
+}
+
+// Slices per block where the plan leaves it open: as many groups as still fill
+// the GPU's 256 compute units at the kernel's waves per SIMD (fewer leave units
+// idle: 8 slices of 256^2 in blocks of one group 13.2 us, of four 27.4), so
+// that a point's coordinates are formed once for all of them (4 slices of
+// 2048^2: blocks of one group 123 us, of two 117; 64 slices: 2923 and, of
+// eight, 2053), but no more than 16 slices of pairs and 6 single ones, beyond
+// which fewer, longer blocks balance worse (64 cubic slices of 2048^2 at P_c =
+// 1: 1100 us with 6, 1227 with 64; 64 of 1024^2: 471 with 16, 528 with 64).
+template <class C>
+static int auto_slices(int batch) {
+    constexpr int kThreads = 256 * 4 * 64 * C::WAVES;
+    constexpr int kMost = C::Q == 2 ? 8 : 6;  // groups
+    const int groups = (batch + C::Q - 1) / C::Q;
+    long long n = (long long)groups * (C::G / 2) * C::T / kThreads;
+    n = n < 1 ? 1 : (n > kMost ? kMost : n);
+    const int chunks = (int)((groups + n - 1) / n);
+    return (groups + chunks - 1) / chunks * C::Q;  // chunks of equal length
+}
+
+template <int LOGG, int TAPS, bool NU, bool TENT>
+static hipError_t launch_gather_k(const GatherArgs& a0, hipStream_t st) {
+    constexpr bool CAN_PIPE = gather_points(1 << LOGG) == 16;
+    constexpr int Q = polar_group(TAPS);
+    using L = GatherKernelCfg<LOGG, TAPS, false>;
+    GatherArgs a = a0;
+    if (a.slices_per_block == 0) a.slices_per_block = auto_slices<L>(a.batch);
+    const int chunks = (a.batch + a.slices_per_block - 1) / a.slices_per_block;
+    if constexpr (CAN_PIPE) {
+        // overlapped only where a block has a second group to overlap
+        if (a.slices_per_block > Q && a.batch > Q) {
+            using C = GatherKernelCfg<LOGG, TAPS, true>;
+            hipLaunchKernelGGL((k_gather_colifft<LOGG, TAPS, NU, TENT, true>), dim3((C::G / 2 + C::F - 1) / C::F, chunks),
+                               dim3(C::WG), 0, st, a);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((k_gather_colifft<LOGG, TAPS, NU, TENT, false>), dim3((L::G / 2 + L::F - 1) / L::F, chunks),
+                       dim3(L::WG), 0, st, a);
+    return hipGetLastError();
 }
 
 template <int LOGG, int TAPS>
 static hipError_t launch_gather_t(const GatherArgs& a, hipStream_t st) {
-    using C = GatherCfg<LOGG, polar_group(TAPS)>;
-    const int cols = C::G / 2;
-    if (a.slices_per_block <= 0 || a.slices_per_block % C::Q != 0) return hipErrorInvalidValue;
-    const int chunks = (a.batch + a.slices_per_block - 1) / a.slices_per_block;
-    dim3 grid((cols + C::F - 1) / C::F, chunks);
+    if (a.slices_per_block < 0 || a.slices_per_block % polar_group(TAPS) != 0) return hipErrorInvalidValue;
     if (a.tent_cols) {
         // tent rule: uniform angles and linear radial taps only (checked by the plan)
-        if constexpr (TAPS == 2)
-            hipLaunchKernelGGL((k_gather_colifft<LOGG, TAPS, false, true>), grid, dim3(C::WG), 0, st, a);
-        else
-            return hipErrorInvalidValue;
-    } else if (a.uniform) {
-        hipLaunchKernelGGL((k_gather_colifft<LOGG, TAPS, false, false>), grid, dim3(C::WG), 0, st, a);
-    } else {
-        hipLaunchKernelGGL((k_gather_colifft<LOGG, TAPS, true, false>), grid, dim3(C::WG), 0, st, a);
+        if constexpr (TAPS == 2) return launch_gather_k<LOGG, TAPS, false, true>(a, st);
+        else return hipErrorInvalidValue;
     }
-    return hipGetLastError();
+    if (a.uniform) return launch_gather_k<LOGG, TAPS, false, false>(a, st);
+    return launch_gather_k<LOGG, TAPS, true, false>(a, st);
 }
 
 static_assert(kTentSlices % kPolarSlices == 0, "a tent group spans whole polar groups");
@@ -784,7 +938,7 @@ hipError_t launch_tent(const bst_plan_s& p, const TentArgs& a, int batch, hipStr
 
 template <int LOGG>
 static hipError_t launch_gather_items_t(const GatherArgs& a, int taps, int blocks, hipStream_t st) {
-    using C = GatherCfg<LOGG, 1, kItemsThreads>;
+    using C = ItemsCfg<LOGG>;
     if (taps == 4) hipLaunchKernelGGL((k_gather_items<LOGG, 4>), dim3(blocks), dim3(C::WG), 0, st, a);
     else hipLaunchKernelGGL((k_gather_items<LOGG, 2>), dim3(blocks), dim3(C::WG), 0, st, a);
     return hipGetLastError();
@@ -809,7 +963,7 @@ hipError_t launch_gather_items(const bst_plan_s& p, const GatherArgs& a, int blo
 
 template <int LOGG>
 static int gather_cols_t() {
-    using C = GatherCfg<LOGG, 1, kItemsThreads>;
+    using C = ItemsCfg<LOGG>;
     return (C::G / 2 + C::F - 1) / C::F;
 }
 

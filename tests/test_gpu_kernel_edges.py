@@ -32,3 +32,28 @@ def test_point_coordinates(P, N, V, P_r, P_c, interp):
     for b in range(2):
         ref = obst.backproject(sino[b].double().cpu().numpy(), Geometry(N, V, N), obst.Params(P_r, P_c, **kw))
         assert_parity(img[b].cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("N,V,P_c,interp,B", [
+    (16, 9, 1, "linear", 5),       # one block holds every column
+    (512, 90, 2, "linear", 3),     # G = 1024: 8 points per thread
+    (512, 90, 4, "keys", 9),       # G = 2048: 16 points, single slices
+    (1024, 91, 2, "linear", 7),    # G = 2048, an odd last pair
+    (1024, 64, 4, "linear", 5),    # G = 4096, a quarter of the rows kept
+    (2048, 65, 1, "keys", 8),      # every row kept
+    (2048, 64, 4, "linear", 3),    # G = 8192
+])
+def test_gather_chunking_is_bitwise(P, N, V, P_c, interp, B):
+    """Blocks of one group, of several with the overlapped gather, ragged last
+    blocks and the default choice give the same bits, and the oracle's values."""
+    print(f"[chunking] N={N} V={V} Pc={P_c} {interp} B={B}", flush=True)
+    kw = {"interp": "keys", "taper": "keys"} if interp == "keys" else {}
+    sino = _sinos(B, V, N, 57 + N + V)
+    ref = P.Plan(N, V, pad_cart=P_c, max_batch=B, **kw).backproject(sino)
+    for gs in (2, 4, 1024):
+        got = P.Plan(N, V, pad_cart=P_c, max_batch=B, gather_slices=gs, **kw).backproject(sino)
+        assert torch.equal(got, ref), gs
+    alone = P.Plan(N, V, pad_cart=P_c, max_batch=1, **kw).backproject(sino[B - 1:])
+    assert torch.equal(alone[0], ref[B - 1])
+    o = obst.backproject(sino[B - 1].double().cpu().numpy(), Geometry(N, V, N), obst.Params(2, P_c, **kw))
+    assert_parity(ref[B - 1].cpu().numpy(), o)
