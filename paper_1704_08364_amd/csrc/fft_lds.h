@@ -31,14 +31,20 @@
 // transforms interleaved lane by lane (thread t serves transform t mod F),
 // contiguous_xor for transforms on contiguous ranges of threads.
 //
-// Inter-pass twiddles: one value w = tw[(jj mod NS) * L/(NS R)] per butterfly
-// from a table tw[k] = exp(-2 pi i k / L) computed in FP64 on the host and
-// rounded to FP32; the other powers w^r are products of its squarings (at most
-// six roundings deep), which replaces R-1 scattered table reads by one
-// coalesced read. The inverse direction conjugates them. The anchors of all
-// passes are read together before the first pass (FftTwiddles), so no pass
-// waits on a table read, and a thread that runs many transforms of one length
-// can read them once and keep them in registers.
+// Inter-pass twiddles: with w = tw[(jj mod NS) * L/(NS R)] of a butterfly, one
+// value w per butterfly (POW = 1) or w and w^4 (POW = 2) come from a table
+// tw[k] = exp(-2 pi i k / L) computed in FP64 on the host and rounded to FP32;
+// the other powers w^r are products of them and their squarings, which replaces
+// R-1 scattered table reads by one or two coalesced ones. With POW = 1 the
+// rounding of w reaches w^8 eight times over. The gather's radix-16 transforms
+// take POW = 2 (their reads serve many transforms): plain backprojections of
+// 1024^2 are then 2.1e-7 from 64 bits, 2.4e-7 otherwise, at equal speed; in
+// kernels of one transform per thread the second read costs 5 % (spectrum of
+// 64 slices of 2048^2: 0.61 -> 0.65 ms).
+// The inverse direction conjugates them. The powers of all passes are read
+// together before the first pass (FftTwiddles), so no pass waits on a table
+// read, and a thread that runs many transforms of one length can read them
+// once and keep them in registers.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -176,10 +182,10 @@ __device__ __forceinline__ void dft(float2* v) {
 // v[k + r*(16/R)] in this thread's registers -- twiddles it by
 // w^((jj mod NS) * r) with w = exp(DIR 2 pi i / (NS R)), transforms, and
 // writes output r to position (jj / NS) * NS * R + (jj mod NS) + r * NS.
-// anc[k]: the twiddle anchor of butterfly k, already conjugated for DIR > 0
+// anc[k]: the twiddles w, w^4 of butterfly k, already conjugated for DIR > 0
 // hook: the caller's work beside the butterflies (see fft)
-template <int L, int DIR, int R, int NS, int E, int PASS, class HOOK>
-__device__ __forceinline__ void stockham_pass(float2 (&v)[E], float2* lds, unsigned off, int j, const float2* anc,
+template <int L, int DIR, int R, int NS, int E, int POW, int PASS, class HOOK>
+__device__ __forceinline__ void stockham_pass(float2 (&v)[E], float2* lds, unsigned off, int j, const float2 (*anc)[POW],
                                               int xm, HOOK& hook) {
     constexpr int T = L / E;
     constexpr int BPT = E / R;
@@ -192,14 +198,12 @@ __device__ __forceinline__ void stockham_pass(float2 (&v)[E], float2* lds, unsig
 #pragma unroll
         for (int r = 0; r < R; ++r) x[r] = v[k + r * BPT];
         if constexpr (NS > 1) {
-            // one table anchor w per butterfly; w^r is the product of the
-            // anchor's binary powers w, w^2, w^4, w^8 picked by the bits of r
-            // (at most three products after at most three squarings), formed
-            // just before use so that few twiddles are live at once
-            const float2 w1 = anc[k];
-            float2 w2 = w1, w4 = w1, w8 = w1;
-            if constexpr (R >= 4) w2 = cmul(w1, w1);
-            if constexpr (R >= 8) w4 = cmul(w2, w2);
+            // w^r is the product of the binary powers w, w^2, w^4, w^8 picked by
+            // the bits of r (at most three products after one squaring),
+            // formed just before use so that few twiddles are live at once
+            const float2 w1 = anc[k][0], w2 = cmul(w1, w1);
+            float2 w4, w8 = w1;
+            if constexpr (POW == 2) w4 = anc[k][1]; else w4 = cmul(w2, w2);
             if constexpr (R >= 16) w8 = cmul(w4, w4);
 #pragma unroll
             for (int r = 1; r < R; ++r) {
@@ -231,10 +235,11 @@ __device__ __forceinline__ void stockham_pass(float2 (&v)[E], float2* lds, unsig
     }
 }
 
-// Twiddle anchors of every pass of one transform of length 2^LOGL held by
-// threads with E values each (the pass plan of fft below): w[p][k] belongs to
-// butterfly k of the p-th pass that has twiddles (the first pass has none).
-template <int LOGL, int DIR, int E>
+// Twiddle powers of every pass of one transform of length 2^LOGL held by
+// threads with E values each (the pass plan of fft below): w[p][k] are w and
+// w^4 of butterfly k of the p-th pass that has twiddles (the first pass has
+// none).
+template <int LOGL, int DIR, int E, int POW = 1>
 struct FftTwiddles {
     static constexpr int L = 1 << LOGL;
     static constexpr int T = L / E;
@@ -249,7 +254,7 @@ struct FftTwiddles {
         return c;
     }
     static constexpr int NT = count();
-    float2 w[NT > 0 ? NT : 1][BPT];
+    float2 w[NT > 0 ? NT : 1][BPT][POW];
 
     __device__ __forceinline__ FftTwiddles(int j, const float2* __restrict__ tw) {
 #pragma unroll
@@ -257,33 +262,39 @@ struct FftTwiddles {
             const int ns = NS0 << (LR * p);
 #pragma unroll
             for (int k = 0; k < BPT; ++k) {
-                const int m = (j + k * T) & (ns - 1);
-                float2 x = tw[m * (L / (ns * R))];
-                if constexpr (DIR > 0) x.y = -x.y;
-                w[p][k] = x;
+                const int m = ((j + k * T) & (ns - 1)) * (L / (ns * R));
+#pragma unroll
+                for (int q = 0; q < POW; ++q) {
+                    float2 x = tw[m << (2 * q)];  // m R <= L and R >= 8
+                    if constexpr (DIR > 0) x.y = -x.y;
+                    w[p][k][q] = x;
+                }
             }
         }
     }
 
-    // Make the anchors opaque to the optimiser at this point. A caller that
-    // runs one transform per loop iteration with loop-invariant anchors calls
+    // Make the powers opaque to the optimiser at this point. A caller that
+    // runs one transform per loop iteration with loop-invariant powers calls
     // this on a copy inside the loop; otherwise every derived power w^r is
     // hoisted out of the loop and held in registers for its whole length.
     __device__ __forceinline__ void pin() {
 #pragma unroll
         for (int p = 0; p < NT; ++p) {
 #pragma unroll
-            for (int k = 0; k < BPT; ++k) asm volatile("" : "+v"(w[p][k].x), "+v"(w[p][k].y));
+            for (int k = 0; k < BPT; ++k) {
+#pragma unroll
+                for (int q = 0; q < POW; ++q) asm volatile("" : "+v"(w[p][k][q].x), "+v"(w[p][k][q].y));
+            }
         }
     }
 };
 
-template <int LOGL, int DIR, int R, int NS, int E, int P, class HOOK>
+template <int LOGL, int DIR, int R, int NS, int E, int P, int POW, class HOOK>
 __device__ __forceinline__ void radix_passes(float2 (&v)[E], float2* lds, unsigned off, int j,
-                                             const FftTwiddles<LOGL, DIR, E>& tw, int xm, HOOK& hook) {
+                                             const FftTwiddles<LOGL, DIR, E, POW>& tw, int xm, HOOK& hook) {
     constexpr int L = 1 << LOGL;
     if constexpr (NS < L) {
-        stockham_pass<L, DIR, R, NS, E, (NS > 1 ? P + 1 : P)>(v, lds, off, j, tw.w[P], xm, hook);
+        stockham_pass<L, DIR, R, NS, E, POW, (NS > 1 ? P + 1 : P)>(v, lds, off, j, tw.w[P], xm, hook);
         radix_passes<LOGL, DIR, R, NS * R, E, (NS > 1 ? P + 1 : P)>(v, lds, off, j, tw, xm, hook);
     }
 }
@@ -306,14 +317,14 @@ constexpr int fft_passes() { return FftTwiddles<LOGL, DIR, E>::NT + 1; }
 // hook(integral_constant<int, i>) is called by every thread before the
 // butterflies of pass i: work of the caller that does not touch the region and
 // that the butterflies' arithmetic can overlap.
-template <int LOGL, int DIR, int E, class HOOK>
+template <int LOGL, int DIR, int E, int POW, class HOOK>
 __device__ __forceinline__ void fft(float2 (&v)[E], float2* lds, unsigned off, int j,
-                                    const FftTwiddles<LOGL, DIR, E>& tw, int xm, HOOK& hook) {
+                                    const FftTwiddles<LOGL, DIR, E, POW>& tw, int xm, HOOK& hook) {
     static_assert(E == 8 || E == 16 || E == 32, "8, 16 or 32 values per thread");
-    using TW = FftTwiddles<LOGL, DIR, E>;
+    using TW = FftTwiddles<LOGL, DIR, E, POW>;
     constexpr int L = 1 << LOGL;
     if constexpr (TW::REM != 0) {
-        stockham_pass<L, DIR, (1 << TW::REM), 1, E, 0>(v, lds, off, j, tw.w[0], xm, hook);
+        stockham_pass<L, DIR, (1 << TW::REM), 1, E, POW, 0>(v, lds, off, j, tw.w[0], xm, hook);
         radix_passes<LOGL, DIR, TW::R, (1 << TW::REM), E, 0>(v, lds, off, j, tw, xm, hook);
     } else {
         radix_passes<LOGL, DIR, TW::R, 1, E, 0>(v, lds, off, j, tw, xm, hook);
@@ -326,7 +337,7 @@ __device__ __forceinline__ void fft(float2 (&v)[E], float2* lds, unsigned off, i
     fft<LOGL, DIR, E>(v, lds, off, j, tw, xm, none);
 }
 
-// The same, reading the twiddle anchors from the table first.
+// The same, reading the twiddle powers from the table first.
 template <int LOGL, int DIR, int E = 16>
 __device__ __forceinline__ void fft(float2 (&v)[E], float2* lds, unsigned off, int j, const float2* __restrict__ tw,
                                     int xm) {

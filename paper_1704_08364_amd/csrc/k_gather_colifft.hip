@@ -436,7 +436,7 @@ __device__ __forceinline__ void gather_body(const GatherArgs& a, int lblock, int
     const AngleView av{V, a.Vs ? (float)((double)V / M_PI) : a.vpi_f, a.Vs ? a.dir + a.ang_off[s_begin] : a.dir};
     const float dc_scale = a.Vs ? a.dc_rule / (float)V : a.dc_scale;
     const bool live = col < G / 2;
-    const FftTwiddles<LOGG, +1, E> tw(j, a.tw);
+    const FftTwiddles<LOGG, +1, E, 2> tw(j, a.tw);
 
     // Stencils, held in registers for the whole chunk of slices. Uniform
     // angles: the table reads of all the thread's points first, so that they
@@ -667,12 +667,12 @@ __device__ __forceinline__ void gather_body(const GatherArgs& a, int lblock, int
             // once and held in registers, which spills.
             int jk = j;
             asm volatile("" : "+v"(jk));
-            FftTwiddles<LOGG, +1, E> twl = tw;
+            FftTwiddles<LOGG, +1, E, 2> twl = tw;
             twl.pin();
             auto hook = [&](auto ph) {
                 if constexpr (MORE) step(std::integral_constant<int, k * (PASSES / Q) + decltype(ph)::value>{});
             };
-            fft<LOGG, +1, E>(cur[k], lds, off, jk, twl, xm, hook);
+            fft(cur[k], lds, off, jk, twl, xm, hook);
             if (live) {
                 float2* D = a.grid + (size_t)(s0 + k) * a.N * a.GT;
                 if (keep == E / 2) store_rows<LOGG, E, E / 2>(cur[k], D, a, jk, col);

@@ -162,7 +162,7 @@ __device__ __forceinline__ void spectrum_body(const SpecArgs& a, int batch, int 
     // between: the data slots of both lines of the first pair (a missing
     // line -- an odd V, or a pair past the end -- reads line 0 and is
     // dropped by a select), the taper, flat and dark, the epilogue weights and
-    // the twiddle anchors; these last are the same for every pair.
+    // the twiddles; these last are the same for every pair.
     auto load_lines = [&](int pair, float (&ra)[NQ], float (&rb)[NQ]) {
         const int ja = 2 * pair, jb = 2 * pair + 1;
         const float* ya = base + (size_t)(ja < Vk ? ja : 0) * a.n;
