@@ -270,14 +270,15 @@ struct RowArgs {
     int N;
     int GT;                     // grid tile-row width (columns)
     float scale;
-    int tiles;                  // row-pair groups per block (set by the launcher)
+    int tiles;                  // row-pair groups per block (ordinary launches: set by the launcher)
     // monopole add-back (mono_part != nullptr): + m amp e^-rho I0(rho),
     // rho = rho_px * ((p - N/2)^2 + (q - N/2)^2)
     const float* mono_part;     // [batch][kMassChunks]
     float mono_inv, mono_amp, mono_rho_px;
     // uneven batches: per-slice projection counts for the monopole mass
     // (mono_inv is for V), and the work list of a persistent launch
-    // ((slice, block) per item)
+    // ((slice, block) per item); n_items: its length, or the row-pair groups of
+    // an ordinary launch (set by the launcher)
     int V;
     const int* Vs;
     const int2* items;

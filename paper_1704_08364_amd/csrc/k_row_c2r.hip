@@ -17,9 +17,9 @@
 
 namespace bst {
 
-// most row-pair groups (8-row tiles) a block walks, for G <= 4096
+// most row-pair groups (8-row tiles; 4 rows past G = 4096) a block walks
 #ifndef BST_ROW_TILES
-#define BST_ROW_TILES 16
+#define BST_ROW_TILES 64
 #endif
 
 // row pairs per block for G <= 4096 (one 8-row tile is 4 pairs)
@@ -33,15 +33,15 @@ struct RowCfg {
     static constexpr int T = G / 16;
     static constexpr int F = G <= 4096 ? BST_ROW_PAIRS : (G == 8192 ? 2 : 1);  // row pairs per block
     static constexpr int WG = F * T;
-    static constexpr int MAX_TILES = G <= 4096 ? BST_ROW_TILES : 1;  // row-pair groups per block, at most
+    static constexpr int MAX_TILES = BST_ROW_TILES;  // row-pair groups per block, at most
     static_assert(T * 16 == G, "16 values per thread");
 };
 
 // MONO: adds m b_phi(u), the closed-form backprojection of the subtracted
 // monopole, to every output pixel.
-// Block (bx, s): row-pair groups bx * tiles .. of slice s.
+// The row-pair groups t0 .. t1 - 1 of the batch, counted slice after slice.
 template <int LOGG, bool MONO>
-__device__ __forceinline__ void row_body(const RowArgs& a, int bx, int s) {
+__device__ __forceinline__ void row_body(const RowArgs& a, int t0, int t1) {
     using C = RowCfg<LOGG>;
     constexpr int G = C::G, T = C::T;
     // one LDS region of G float2 per row pair, the pairs' lanes interleaved
@@ -52,34 +52,35 @@ __device__ __forceinline__ void row_body(const RowArgs& a, int bx, int s) {
     const int j = threadIdx.x / C::F;
     const unsigned my_off = (unsigned)(fid * G) * 8u;
     const int xm = region_xor<LOGG, C::F>(fid);
-    const int groups = a.N / (2 * C::F);             // row-pair groups (tiles) per slice
-    const int g0 = bx * a.tiles;
-    float* const img_s = a.img_list ? a.img_list[s] : a.img + (size_t)s * a.N * a.N;
+    const int log_groups = __ffs(a.N / (2 * C::F)) - 1;  // row-pair groups per slice, a power of two
     const FftTwiddles<LOGG, +1, 16> tw(j, a.tw);
     float mamp = 0.f;
-    if constexpr (MONO) {
-        const float inv = a.Vs ? a.mono_inv * (float)a.V / (float)a.Vs[s] : a.mono_inv;
-        mamp = monopole_mass(a.mono_part, s, inv) * a.mono_amp;
-    }
+    int mslice = -1;  // the slice mamp belongs to
 
     // Thread j's slots e < 8 are k = j + e*T < G/2: the block reads every
     // stored column once (all loads first, no branch between them) and puts
     // it in LDS, where the Hermitian extension k > G/2 (the conjugate of
-    // column G - k) is read back; k = G/2 is zero. A block walks TILES
-    // groups, the next group's reads in flight during the current group's
-    // transform.
-    auto load = [&](int grp, float4 (&q)[8]) {
-        const int row0 = (grp < groups ? grp : 0) * (2 * C::F) + 2 * fid;
+    // column G - k) is read back; k = G/2 is zero. The next group's reads are
+    // in flight during the current group's transform.
+    auto load = [&](int t, float4 (&q)[8]) {
+        const int row0 = (t & ((1 << log_groups) - 1)) * (2 * C::F) + 2 * fid;
         const float4* tile = reinterpret_cast<const float4*>(
-            a.grid + ((size_t)s * a.N + (size_t)(row0 >> 3) * 8) * a.GT);
+            a.grid + ((size_t)(t >> log_groups) * a.N + (size_t)(row0 >> 3) * 8) * a.GT);
 #pragma unroll
         for (int e = 0; e < 8; ++e) q[e] = tile[BST_IDX((j + e * T) * 4 + ((row0 & 7) >> 1), 4 * a.GT, 0)];
     };
     float4 q[8];
-    load(g0, q);
+    load(t0, q);
 #pragma unroll 1
-    for (int it = 0; it < a.tiles; ++it) {
-        const int grp = g0 + it;
+    for (int t = t0; t < t1; ++t) {
+        const int s = t >> log_groups;
+        if constexpr (MONO) {
+            if (s != mslice) {
+                const float inv = a.Vs ? a.mono_inv * (float)a.V / (float)a.Vs[s] : a.mono_inv;
+                mamp = monopole_mass(a.mono_part, s, inv) * a.mono_amp;
+                mslice = s;
+            }
+        }
         int jv = j;
         asm volatile("" : "+v"(jv));
         float4* stage = reinterpret_cast<float4*>(lds);  // [G/2][F] of the group's row pairs
@@ -102,42 +103,41 @@ __device__ __forceinline__ void row_body(const RowArgs& a, int bx, int s) {
             v[e] = make_float2(x0.x - x1.y, x0.y + x1.x);
         }
         __syncthreads();  // the transform overwrites the staged columns
-        if (it + 1 < a.tiles) load(grp + 1, q);
+        if (t + 1 < t1) load(t + 1, q);
 
         FftTwiddles<LOGG, +1, 16> twl = tw;
         twl.pin();
         fft<LOGG, +1>(v, lds, my_off, jv, twl, xm);
 
-        if (grp < groups) {
-            const int row0 = BST_IDX(grp * (2 * C::F) + 2 * fid, a.N - 1, 1);
-            float* o0 = img_s + (size_t)row0 * a.N;
-            float* o1 = o0 + a.N;
-            const int half_n = a.N >> 1;
+        const int row0 = BST_IDX((t & ((1 << log_groups) - 1)) * (2 * C::F) + 2 * fid, a.N - 1, 1);
+        float* o0 = (a.img_list ? a.img_list[s] : a.img + (size_t)s * a.N * a.N) + (size_t)row0 * a.N;
+        float* o1 = o0 + a.N;
+        const int half_n = a.N >> 1;
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int x = jv + e * T;
-                const int c = (x + half_n) & (G - 1);
-                if (c < a.N) {
-                    float b0 = v[e].x * a.scale, b1 = v[e].y * a.scale;
-                    if constexpr (MONO) {
-                        // pixel offsets from the centre: exact in float (|.|^2 <= 2^23)
-                        const float dx = (float)(c - half_n), dy = (float)(row0 - half_n);
-                        const float r0 = dx * dx + dy * dy;
-                        const float r1 = r0 + 2.f * dy + 1.f;
-                        b0 += mamp * scaled_bessel_i0(a.mono_rho_px * r0);
-                        b1 += mamp * scaled_bessel_i0(a.mono_rho_px * r1);
-                    }
-                    o0[BST_IDX(c, a.N, 2)] = b0;
-                    o1[BST_IDX(c, a.N, 2)] = b1;
+        for (int e = 0; e < 16; ++e) {
+            const int x = jv + e * T;
+            const int c = (x + half_n) & (G - 1);
+            if (c < a.N) {
+                float b0 = v[e].x * a.scale, b1 = v[e].y * a.scale;
+                if constexpr (MONO) {
+                    // pixel offsets from the centre: exact in float (|.|^2 <= 2^23)
+                    const float dx = (float)(c - half_n), dy = (float)(row0 - half_n);
+                    const float r0 = dx * dx + dy * dy;
+                    const float r1 = r0 + 2.f * dy + 1.f;
+                    b0 += mamp * scaled_bessel_i0(a.mono_rho_px * r0);
+                    b1 += mamp * scaled_bessel_i0(a.mono_rho_px * r1);
                 }
+                o0[BST_IDX(c, a.N, 2)] = b0;
+                o1[BST_IDX(c, a.N, 2)] = b1;
             }
         }
     }
 }
 
 template <int LOGG, bool MONO>
-__global__ void __launch_bounds__(RowCfg<LOGG>::WG) k_row_c2r(RowArgs a) {
-    row_body<LOGG, MONO>(a, blockIdx.x, blockIdx.y);
+__global__ void __launch_bounds__(RowCfg<LOGG>::WG) __attribute__((amdgpu_waves_per_eu(4, 8))) k_row_c2r(RowArgs a) {
+    const int t0 = blockIdx.x * a.tiles;
+    row_body<LOGG, MONO>(a, t0, min(t0 + a.tiles, a.n_items));
 }
 
 // Persistent launch of uneven batches: every block walks the work list
@@ -150,7 +150,9 @@ __global__ void __launch_bounds__(RowCfg<LOGG>::WG) k_row_items(RowArgs a) {
         if (it >= a.n_items) break;
         const int2 w = a.items[it];
         __syncthreads();  // the previous item's LDS reads are done
-        row_body<LOGG, MONO>(a, w.y, w.x);
+        const int groups = a.N / (2 * RowCfg<LOGG>::F);
+        const int first = w.y * a.tiles;
+        row_body<LOGG, MONO>(a, w.x * groups + first, w.x * groups + min(first + a.tiles, groups));
     }
 }
 
@@ -158,13 +160,18 @@ template <int LOGG>
 static hipError_t launch_row_t(const RowArgs& a0, int batch, hipStream_t st) {
     using C = RowCfg<LOGG>;
     RowArgs a = a0;
-    const int groups = a.N / (2 * C::F);
-    // as many groups per block as keep about four blocks per compute unit
-    constexpr int kTargetBlocks = 1024;
-    int tiles = (int)(((long long)groups * batch) / kTargetBlocks);
-    tiles = tiles < 1 ? 1 : (tiles > C::MAX_TILES ? C::MAX_TILES : tiles);
-    a.tiles = tiles;
-    dim3 grid((groups + tiles - 1) / tiles, batch);
+    // one block per slot of the GPU (256 compute units of 16 waves), each walking
+    // an equal share of the batch's groups, so that the reads of all but its
+    // first group hide behind a transform. With shares of whole slices and
+    // about four blocks per unit, part rounds and unhidden reads took 7 slices
+    // of 2048^2 106 us (now 88), 24 of 1024^2 73 (65), 16 with the monopole 73
+    // (59), 2 of 4096^2 156 (131); 64 of 2048^2 are unchanged at 0.60 ms (5.4
+    // TB/s, the rate of a copy).
+    constexpr int kSlots = 256 * 1024 / (C::WG > 64 ? C::WG : 64);
+    a.n_items = a.N / (2 * C::F) * batch;  // groups of the batch
+    a.tiles = (a.n_items + kSlots - 1) / kSlots;
+    if (a.tiles > C::MAX_TILES) a.tiles = C::MAX_TILES;
+    const dim3 grid((a.n_items + a.tiles - 1) / a.tiles);
     if (a.mono_part) hipLaunchKernelGGL((k_row_c2r<LOGG, true>), grid, dim3(C::WG), 0, st, a);
     else hipLaunchKernelGGL((k_row_c2r<LOGG, false>), grid, dim3(C::WG), 0, st, a);
     return hipGetLastError();

@@ -57,3 +57,24 @@ def test_gather_chunking_is_bitwise(P, N, V, P_c, interp, B):
     assert torch.equal(alone[0], ref[B - 1])
     o = obst.backproject(sino[B - 1].double().cpu().numpy(), Geometry(N, V, N), obst.Params(2, P_c, **kw))
     assert_parity(ref[B - 1].cpu().numpy(), o)
+
+
+@pytest.mark.parametrize("N,V,filt,mono,B", [
+    (16, 9, "ramp", 0.0, 3),       # one group a block, several slices in flight
+    (2048, 33, "ramp", 0.0, 7),    # blocks of seven groups, across slices
+    (2048, 33, "none", 0.4, 7),    # the monopole of each slice a block walks
+    (4096, 17, "ramp", 0.0, 3),    # groups of four rows, the last block short
+    (512, 50, "none", 0.4, 33),
+])
+def test_row_blocks_across_slices(P, N, V, filt, mono, B):
+    """Row blocks that walk several slices: every slice as when it runs alone,
+    and the oracle's values."""
+    print(f"[row blocks] N={N} V={V} {filt} B={B}", flush=True)
+    plan = P.Plan(N, V, filter=filt, monopole_width=mono, max_batch=B)
+    sino = _sinos(B, V, N, 91 + N + B)
+    img = plan.backproject(sino)
+    for b in range(B):
+        assert torch.equal(plan.backproject(sino[b:b + 1])[0], img[b]), b
+    ref = obst.backproject(sino[B - 1].double().cpu().numpy(), Geometry(N, V, N),
+                           obst.Params(filter=filt, monopole=mono))
+    assert_parity(img[B - 1].cpu().numpy(), ref)
