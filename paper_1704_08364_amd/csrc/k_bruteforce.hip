@@ -118,33 +118,99 @@ __global__ void __launch_bounds__(256) k_bruteforce(BfArgs a) {
 
 // Ramp filter of the brute-force FBP: the band-limited spatial kernel of Kak
 // and Slaney sampled at the detector pitch, applied as a linear (not circular)
-// convolution, q[i] = dt sum_k h[i - k] y[k] over the n bins. Only d = 0 and
-// odd distances d carry weight. One block per projection; the row is staged
-// in LDS in FP64 and every output sums its terms in FP64 in a fixed order.
-constexpr int kRampThreads = 256;
+// convolution, q[i] = dt sum_k h[i - k] y[k] over the n bins, in FP64. Only
+// d = 0 and odd distances d carry weight, so the even outputs 2p take the odd
+// samples 2q + 1 and the odd outputs the even samples, each a product with a
+// Toeplitz matrix,
+//   out[2p]     = h[0] y[2p]     + sum_q E[p - q]     y[2q + 1],
+//   out[2p + 1] = h[0] y[2p + 1] + sum_q E[p - q + 1] y[2q],   E[x] = h[|2x - 1|],
+// which runs on the FP64 matrix units: A = 16 projections x 4 samples, B = 4
+// samples x 16 outputs. Bound by their rate (V n^2 multiply-adds a slice: 27 us
+// for 2 slices of 1024 x 1024 bins; one thread per output, two LDS reads per
+// multiply-add, took 320 us, this 50).
+// A block takes kRampRows projections and kRampOut output pairs, a wave 32 of
+// them in both parities (so that lanes store whole lines); E's window and
+// chunks of kRampChunk sample pairs are staged in LDS, samples as doubles with
+// row strides that put a wave's 16 rows x 4 samples on distinct banks. Samples
+// past n / 2 are zero and outputs past it are dropped.
+constexpr int kRampThreads = 256, kRampRows = 16, kRampOut = 128, kRampChunk = 64;
+constexpr int kRampStride = kRampChunk + 2;
+
+__host__ __device__ constexpr int ramp_pad(int n) { return (n / 2 + kRampChunk - 1) / kRampChunk * kRampChunk; }
 
 __global__ void __launch_bounds__(kRampThreads) k_ramp_filter(RampArgs a) {
-    extern __shared__ double row[];
-    const int j = blockIdx.x, s = blockIdx.y;
-    const float* y = a.sino + ((size_t)s * a.V + j) * a.n;
-    for (int i = threadIdx.x; i < a.n; i += kRampThreads) row[i] = (double)y[i];
-    __syncthreads();
-    float* q = a.out + ((size_t)s * a.V + j) * a.n;
-    for (int i = threadIdx.x; i < a.n; i += kRampThreads) {
-        double acc = a.h[0] * row[i];
-        // odd distances d: the samples i - d and i + d that exist
-        for (int d = 1; d < a.n; d += 2) {
-            const double l = i - d >= 0 ? row[i - d] : 0.0;
-            const double r = i + d < a.n ? row[i + d] : 0.0;
-            acc = fma(a.h[d], l + r, acc);
+    typedef double d4 __attribute__((ext_vector_type(4)));
+    typedef float f2 __attribute__((ext_vector_type(2), aligned(4)));  // rows start at any float
+    __shared__ double ys[2][kRampRows][kRampStride];  // [parity of the sample][projection][q]
+    extern __shared__ double toep[];                  // E[P0 - qpad + 1 + i], qpad + kRampOut values
+    const int half = a.n >> 1, qpad = ramp_pad(a.n);
+    const int row0 = blockIdx.x * kRampRows, P0 = blockIdx.y * kRampOut;
+    const float* Y = a.sino + (size_t)blockIdx.z * a.V * a.n;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, lo = lane & 15, hi = lane >> 4;
+    for (int i = threadIdx.x; i < qpad + kRampOut; i += kRampThreads) {
+        const int x = 2 * (P0 - qpad + 1 + i) - 1;
+        const int d = x < 0 ? -x : x;
+        toep[i] = d < a.n ? a.h[d] : 0.0;
+    }
+    // a chunk's sample pairs: thread t reads pairs t % 64 of projections t / 64 + 4 k
+    constexpr int PER = kRampRows * kRampChunk / kRampThreads;
+    f2 y[PER];
+    auto load = [&](int q0) {
+        const int q = q0 + (threadIdx.x % kRampChunk);
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int r = min(row0 + (int)threadIdx.x / kRampChunk + k * (kRampThreads / kRampChunk), a.V - 1);
+            y[k] = reinterpret_cast<const f2*>(Y + (size_t)r * a.n)[q < half ? q : 0];
+            if (q >= half) y[k] = f2{0.f, 0.f};
         }
-        q[i] = (float)acc;
+    };
+    d4 even[2], odd[2];  // outputs p0 + 16 t + lo of both parities, projections hi + 4 r
+#pragma unroll
+    for (int t = 0; t < 2; ++t) even[t] = odd[t] = d4{0.0, 0.0, 0.0, 0.0};
+    const int p0 = wave * 32;  // in the block
+    load(0);
+    for (int q0 = 0; q0 < qpad; q0 += kRampChunk) {
+        __syncthreads();  // the previous chunk is used up
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const int r = threadIdx.x / kRampChunk + k * (kRampThreads / kRampChunk), q = threadIdx.x % kRampChunk;
+            ys[0][r][q] = (double)y[k].x;
+            ys[1][r][q] = (double)y[k].y;
+        }
+        __syncthreads();
+        if (q0 + kRampChunk < qpad) load(q0 + kRampChunk);
+        const double* e = toep + p0 + lo - (q0 + hi) + qpad - 1;
+#pragma unroll 4
+        for (int q = 0; q < kRampChunk; q += 4) {
+            const double ae = ys[0][lo][q + hi], ao = ys[1][lo][q + hi];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                even[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(ao, e[16 * t - q], even[t], 0, 0, 0);
+                odd[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(ae, e[16 * t - q + 1], odd[t], 0, 0, 0);
+            }
+        }
+    }
+    float* out = a.out + (size_t)blockIdx.z * a.V * a.n;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int p = P0 + p0 + 16 * t + lo;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int j = row0 + hi + 4 * r;
+            if (p < half && j < a.V) {
+                const f2 c = reinterpret_cast<const f2*>(Y + (size_t)j * a.n)[p];
+                reinterpret_cast<f2*>(out + (size_t)j * a.n)[p] =
+                    f2{(float)fma(a.h[0], (double)c.x, even[t][r]), (float)fma(a.h[0], (double)c.y, odd[t][r])};
+            }
+        }
     }
 }
 
 hipError_t launch_ramp_filter(const bst_plan_s& p, const RampArgs& a, int batch, hipStream_t st) {
     (void)p;
-    hipLaunchKernelGGL(k_ramp_filter, dim3(a.V, batch), dim3(kRampThreads), a.n * sizeof(double), st, a);
+    const int qpad = ramp_pad(a.n);
+    const dim3 grid((a.V + kRampRows - 1) / kRampRows, (a.n / 2 + kRampOut - 1) / kRampOut, batch);
+    hipLaunchKernelGGL(k_ramp_filter, grid, dim3(kRampThreads), (size_t)(qpad + kRampOut) * sizeof(double), st, a);
     return hipGetLastError();
 }
 

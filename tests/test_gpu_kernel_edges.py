@@ -6,6 +6,7 @@ import pytest
 import torch
 
 from oracle import bst as obst
+from oracle import ramp as oramp
 from oracle.geometry import Geometry
 from test_gpu_parity import DEV, P, _sinos, assert_parity  # noqa: F401
 
@@ -78,3 +79,28 @@ def test_row_blocks_across_slices(P, N, V, filt, mono, B):
     ref = obst.backproject(sino[B - 1].double().cpu().numpy(), Geometry(N, V, N),
                            obst.Params(filter=filt, monopole=mono))
     assert_parity(img[B - 1].cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("n,V,B,offset", [
+    (16, 1 + 1, 1, 0),    # fewer outputs and projections than a tile
+    (32, 17, 2, 1),       # one projection past a tile; rows at odd floats
+    (256, 16, 1, 0),      # exactly one tile of projections, one block of outputs
+    (512, 31, 3, 1),
+    (4096, 18, 1, 0),     # the longest row
+])
+def test_ramp_filter_tiles(P, n, V, B, offset):
+    """The FP64 matrix-unit ramp at the edges of its tiles: within float
+    rounding (2^-24 of the output's own scale) of the FP64 convolution."""
+    print(f"[ramp] n={n} V={V} B={B} offset={offset}", flush=True)
+    plan = P.Plan(n, V, max_batch=B)
+    buf = torch.randn(B * V * n + 2, generator=torch.Generator().manual_seed(n + V)).to(DEV)
+    sino = buf[offset:offset + B * V * n].view(B, V, n)
+    out = torch.full((B * V * n + 2,), 7.0, device=DEV)
+    plan.ramp_filter(sino, out=out[offset:offset + B * V * n].view(B, V, n))
+    torch.cuda.synchronize()
+    got = out.cpu().double().numpy()
+    assert np.all(got[:offset] == 7.0) and np.all(got[offset + B * V * n:] == 7.0)
+    y = sino.cpu().double().numpy()
+    ref = np.stack([oramp.filter_fft(v, 2.0 / n) for v in y])
+    err = np.abs(got[offset:offset + B * V * n].reshape(ref.shape) - ref)
+    assert np.all(err <= 2.0 ** -23 * np.abs(ref) + 1e-12 * np.abs(ref).max())
