@@ -216,7 +216,8 @@ __device__ __forceinline__ int angle_guess(int col, int bs, const AngleView& av)
 
 // Stencil of Cartesian point (col, bs); bs signed. NU: non-uniform angles.
 // SERIES: uniform, at least kSeriesAngles angles. guess, cs: the angle index
-// from angle_guess and its table entry (uniform angles).
+// from angle_guess and its table entry (uniform angles). mirror: also the
+// stencil of (col, -bs) (SERIES, bs >= 0, not the tent rule's wide points).
 // TENT: a wide point of the tent rule (|bs| <= B_col) gets bit 31 of o0 and
 // its patch slot in the low bits; its polar reads go to the zero slots.
 template <bool TILED>
@@ -231,7 +232,7 @@ __device__ __forceinline__ unsigned sample_code(const GatherArgs& a, int j, int 
 
 template <bool NU, bool TENT, bool TILED, bool SERIES>
 __device__ __forceinline__ Stencil point_stencil(int col, int bs, const GatherArgs& a, const AngleView& av,
-                                                 int guess, float4 cs) {
+                                                 int guess, float4 cs, Stencil* mirror = nullptr) {
     // points without a stencil of their own: the origin, radii past the data
     Stencil none;
     none.o0 = sample_code<TILED>(a, 0, a.zero_slot);
@@ -334,6 +335,16 @@ __device__ __forceinline__ Stencil point_stencil(int col, int bs, const GatherAr
     st.o0 = sample_code<TILED>(a, j0, m0) | ((unsigned)flip0 << 31);
     st.g = __uint_as_float(__float_as_uint(g) | ((unsigned)wrap << 31));
     st.w1 = conj1 ? -f : f;
+    if (mirror) {
+        // (a, -b), b > 0: direction pi - theta, between the angles V - 1 - j0
+        // and V - j0 at fraction 1 - f, all of it conjugated but the image past
+        // theta_{V-1}
+        const bool mwrap = j0 == 0;
+        mirror->o0 = sample_code<TILED>(a, av.V - 1 - j0, m0);
+        mirror->g = __uint_as_float(__float_as_uint(g) | ((unsigned)mwrap << 31));
+        mirror->w1 = mwrap ? 1.f - f : f - 1.f;
+        if (empty) *mirror = none;
+    }
     return empty ? none : st;
 }
 
@@ -450,16 +461,51 @@ __device__ __forceinline__ void gather_body(const GatherArgs& a, int lblock, int
         return live ? (b < G / 2 ? b : b - G) : 0;
     };
     if (!NU && V >= kSeriesAngles) {
-        int guess[E];
-        float4 cs[E];
+        // the upper half-plane's rows, and from each its mirror image, which
+        // thread T - j (of the same column) takes over through LDS: row b of
+        // thread j and point e is row -b of thread T - j and point E - 1 - e
+        // (of thread 0 and point E - e for j = 0)
+        constexpr int H = E / 2;
+        static_assert(C::NREG * C::REGION * 2 >= C::WG * H * 3, "the exchange needs LDS");
+        unsigned* xch = reinterpret_cast<unsigned*>(lds);
+        int guess[H];
+        float4 cs[H];
 #pragma unroll
-        for (int e = 0; e < E; ++e) {
+        for (int e = 0; e < H; ++e) {
             guess[e] = angle_guess(c, row(e), av);
             cs[e] = av.dir[guess[e]];
         }
 #pragma unroll
-        for (int e = 0; e < E; ++e)
-            pt[e] = point_stencil<NU, TENT, TILED, true>(c, row(e), a, av, guess[e], cs[e]);
+        for (int e = 0; e < H; ++e) {
+            Stencil m;
+            pt[e] = point_stencil<NU, TENT, TILED, true>(c, row(e), a, av, guess[e], cs[e], &m);
+            unsigned* d = xch + (e * 3) * C::WG + threadIdx.x;
+            d[0] = m.o0;
+            d[C::WG] = __float_as_uint(m.g);
+            d[2 * C::WG] = __float_as_uint(m.w1);
+        }
+        __syncthreads();
+        const int from = (j == 0 ? 0 : (T - j) * F) + fid;
+#pragma unroll
+        for (int e = H; e < E; ++e) {
+            const int se = j == 0 ? min(E - e, H - 1) : E - 1 - e;
+            const unsigned* d = xch + (se * 3) * C::WG + from;
+            pt[e].o0 = d[0];
+            pt[e].g = __uint_as_float(d[C::WG]);
+            pt[e].w1 = __uint_as_float(d[2 * C::WG]);
+            if constexpr (TENT) {
+                const int2 tc = a.tent_cols[c];
+                if (live && row(e) >= -tc.y) {
+                    pt[e].o0 = (unsigned)(tc.x + row(e) + tc.y) | 0x80000000u;
+                    pt[e].g = pt[e].w1 = 0.f;
+                }
+            }
+        }
+        if (j == 0) {  // row -G/2 has no mirror image in the grid
+            const int g0 = angle_guess(c, row(H), av);
+            pt[H] = point_stencil<NU, TENT, TILED, true>(c, row(H), a, av, g0, av.dir[g0]);
+        }
+        __syncthreads();  // the transforms reuse this LDS
     } else {
         constexpr int CH = 2;
         constexpr int NW = 3;  // words per stencil

@@ -104,3 +104,25 @@ def test_ramp_filter_tiles(P, n, V, B, offset):
     ref = np.stack([oramp.filter_fft(v, 2.0 / n) for v in y])
     err = np.abs(got[offset:offset + B * V * n].reshape(ref.shape) - ref)
     assert np.all(err <= 2.0 ** -23 * np.abs(ref) + 1e-12 * np.abs(ref).max())
+
+
+@pytest.mark.parametrize("N,angles", [
+    (64, [0.0, 3.1415926]),                       # two angles at the ends
+    (64, [1.5707963267948966 - 1e-9, 1.5707963267948966]),   # a gap below the search table's step
+    (128, list(np.arange(128) * 1e-6 + 1.0) + [3.0]),        # a whole cluster in one bucket
+    (128, list(np.sort(np.mod(np.arange(90) * 1.9416135460476904, np.pi)))),
+    (64, list(np.arange(40) * (np.pi / 40))),                # directions exactly on angles
+])
+def test_angle_search(P, N, angles):
+    """The bracketing angle of every direction, from the search table: two
+    angles, clusters inside a bucket, directions on an angle."""
+    print(f"[angle search] N={N} V={len(angles)}", flush=True)
+    V = len(angles)
+    th = np.asarray(angles)
+    plan = P.Plan(N, V, angles=th, max_batch=2)
+    sino = _sinos(2, V, N, 7 + N + V)
+    img = plan.backproject(sino)
+    torch.cuda.synchronize()
+    for b in range(2):
+        ref = obst.backproject(sino[b].double().cpu().numpy(), Geometry(N, V, N, angles=th), obst.Params())
+        assert_parity(img[b].cpu().numpy(), ref)
