@@ -399,6 +399,11 @@ bst_status bst_plan(const bst_params* p, bst_plan_t* out) {
         const double next = (j == V - 1) ? theta[0] + M_PI : theta[j + 1];
         inv_gap[j] = (float)(1.0 / (next - theta[j]));
     }
+    // non-uniform angles: how many lie at or below each bucket edge
+    const int buckets = pl->uniform ? 0 : bst::angle_buckets(V);
+    std::vector<int> below(buckets + 1, 0);
+    for (int k = 0; k <= buckets && !pl->uniform; ++k)
+        below[k] = (int)(std::upper_bound(theta.begin(), theta.end(), (double)k * M_PI / (double)buckets) - theta.begin());
     for (int j = 0; j < V; ++j) {
         bf_c[j] = std::cos(theta[j]) * ratio;
         bf_s[j] = std::sin(theta[j]) * ratio;
@@ -444,6 +449,7 @@ bst_status bst_plan(const bst_params* p, bst_plan_t* out) {
     const size_t o_ang = off;   off = up(off + V * sizeof(double2));
     const size_t o_dir = off;   off = up(off + V * sizeof(float4));
     const size_t o_gap = off;   off = up(off + V * sizeof(float));
+    const size_t o_below = off; off = up(off + below.size() * sizeof(int));
     const size_t o_prow = off;  off = up(off + V * sizeof(float));
     const size_t o_mphi = off;  off = up(off + n * sizeof(float));
     const size_t o_ramp = off;  off = up(off + n * sizeof(double));
@@ -461,6 +467,7 @@ bst_status bst_plan(const bst_params* p, bst_plan_t* out) {
     std::memcpy(host.data() + o_ang, ang.data(), V * sizeof(double2));
     std::memcpy(host.data() + o_dir, dir.data(), V * sizeof(float4));
     std::memcpy(host.data() + o_gap, inv_gap.data(), V * sizeof(float));
+    std::memcpy(host.data() + o_below, below.data(), below.size() * sizeof(int));
     std::memcpy(host.data() + o_prow, proj_row.data(), V * sizeof(float));
     std::memcpy(host.data() + o_mphi, mono_phi.data(), n * sizeof(float));
     // band-limited ramp of the brute-force comparison (Kak and Slaney): h[0] =
@@ -570,6 +577,7 @@ bst_status bst_plan(const bst_params* p, bst_plan_t* out) {
     pl->ang = reinterpret_cast<double2*>(base + o_ang);
     pl->dir = reinterpret_cast<float4*>(base + o_dir);
     pl->inv_gap = reinterpret_cast<float*>(base + o_gap);
+    pl->ang_below = reinterpret_cast<int*>(base + o_below);
     pl->proj_row = reinterpret_cast<float*>(base + o_prow);
     pl->mono_phi = reinterpret_cast<float*>(base + o_mphi);
     pl->ramp_h = reinterpret_cast<double*>(base + o_ramp);
@@ -696,6 +704,8 @@ bst_status run_backproject(bst_plan_t plan, const float* sino, float* img, int32
     ga.ang = plan->ang;
     ga.dir = plan->dir;
     ga.inv_gap = plan->inv_gap;
+    ga.ang_below = plan->ang_below;
+    ga.ang_buckets = plan->uniform ? 0 : bst::angle_buckets(plan->V);
     ga.uniform = plan->uniform ? 1 : 0;
     ga.dc_scale = plan->dc_scale;
     if (plan->tent) {

@@ -49,6 +49,7 @@ struct bst_plan_s {
     double2* ang;        // [V]          (cos theta_j, sin theta_j), non-uniform angles' residuals
     float4* dir;         // [V]          the same as FP32 pairs (split_direction), uniform angles
     float* inv_gap;      // [V]          1 / (theta_{j+1} - theta_j), last gap to theta_0 + pi
+    int* ang_below;      // [K + 1]      angles theta_j <= k pi / K, k = 0 .. K (angle_buckets(V))
     // adjoint (bst_project): transposed gather as CSR lists per polar sample
     bool adjoint;
     void* adj_block;
@@ -223,6 +224,8 @@ struct GatherArgs {
     const double2* ang;      // [V] (cos theta_j, sin theta_j), non-uniform angles
     const float4* dir;       // [V] the same as FP32 pairs (split_direction), uniform angles
     const float* inv_gap;    // [V] 1 / angle gap (non-uniform angles)
+    const int* ang_below;    // [K + 1] angles theta_j <= k pi / K (non-uniform angles)
+    int ang_buckets;         // K
     int uniform;             // angles are j pi / V
     // tent angular rule (tent_cols != nullptr): wide points read their value
     // from the pre-gathered patch [batch][tent_w] instead of the polar rows
@@ -241,6 +244,13 @@ struct GatherArgs {
     int n_items;
 };
 
+// Buckets of the search table of a non-uniform angle set: about four per angle,
+// so that a direction's neighbours are found in one or two steps.
+inline int angle_buckets(int V) {
+    int k = 8;
+    while (k < 4 * V) k *= 2;
+    return k;
+}
 // the radius scale P_r / P_c, a power of two between 1/4 and 4
 inline void set_radius_scale(GatherArgs& a, double rscale) {
     a.rshift = std::ilogb(rscale);
