@@ -44,39 +44,40 @@ template <int LOGG>
 __global__ void __launch_bounds__(ProjRowCfg<LOGG>::WG) k_proj_rows(ProjRowArgs a) {
     using C = ProjRowCfg<LOGG>;
     constexpr int G = C::G, T = C::T;
-    __shared__ float2 lds[C::F * G];  // one region per row pair, the pairs' lanes interleaved
-    const int fid = threadIdx.x % C::F;
-    const int j = threadIdx.x / C::F;
-    const unsigned my_off = (unsigned)(fid * G) * 8u;
-    const int xm = region_xor<LOGG, C::F>(fid);
-    const int row0 = blockIdx.x * (2 * C::F) + 2 * fid;
-    const int s = blockIdx.y;
-    const float* r0 = a.img + ((size_t)s * a.N + row0) * a.N;
-    const float* r1 = r0 + a.N;
-    const int half_n = a.N >> 1;
-
-    // loads first, branch-free: columns outside the crop read column 0 and
-    // are replaced by zero
-    float x0[16], x1[16];
+    __shared__ float2 lds[C::F * G];  // one region per row pair
+    const int s = blockIdx.y, rows = blockIdx.x * (2 * C::F);
+    const int keep = 8 * a.N / G;  // the crop: points e < keep and e >= 16 - keep
+    {
+        // transform: row pair u on T consecutive threads, so that a wave reads
+        // whole lines of a row (with the pairs interleaved lane by lane every
+        // read touched four rows and the texture path, not memory, bound the
+        // kernel: 32 slices of 1024^2 95 -> 66 us)
+        const int u = threadIdx.x / T, j = threadIdx.x % T;
+        const unsigned off = (unsigned)(u * G) * 8u;
+        const int xm = region_xor<LOGG, C::F>(u);
+        const float* r0 = a.img + ((size_t)s * a.N + rows + 2 * u) * a.N;
+        float2 v[16];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const int q = (j + e * T + half_n) & (G - 1);
-        const int qq = q < a.N ? q : 0;
-        x0[e] = r0[qq];
-        x1[e] = r1[qq];
+        for (int e = 0; e < 16; ++e) {
+            v[e] = make_float2(0.f, 0.f);
+            if (e < keep || e >= 16 - keep) {
+                const int q = j + e * T + (e < keep ? a.N / 2 : a.N / 2 - G);
+                v[e] = make_float2(r0[BST_IDX(q, a.N, 3)], r0[a.N + BST_IDX(q, a.N, 3)]);
+            }
+        }
+        fft<LOGG, -1>(v, lds, off, j, a.tw, xm);
+        const unsigned pj = lds_byte(off, lds_swz<16>(j), xm);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) lds_at(lds, pj ^ swz_bytes<16>(e * T)) = v[e];
     }
-    float2 v[16];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const int q = (j + e * T + half_n) & (G - 1);
-        v[e] = q < a.N ? make_float2(x0[e], x1[e]) : make_float2(0.f, 0.f);
-    }
-    fft<LOGG, -1>(v, lds, my_off, j, a.tw, xm);
-    const unsigned pj = lds_byte(my_off, lds_swz<16>(j), xm);
-#pragma unroll
-    for (int e = 0; e < 16; ++e) lds_at(lds, pj ^ swz_bytes<16>(e * T)) = v[e];
     __syncthreads();
 
+    // split and store: the pairs interleaved lane by lane, which fills the
+    // 8-row tiles' lines
+    const int fid = threadIdx.x % C::F, j = threadIdx.x / C::F;
+    const unsigned my_off = (unsigned)(fid * G) * 8u;
+    const int xm = region_xor<LOGG, C::F>(fid);
+    const int row0 = rows + 2 * fid;
     float4* tile = reinterpret_cast<float4*>(a.grid + ((size_t)s * a.N + (size_t)(row0 >> 3) * 8) * (G / 2));
     const int sub = row0 & 7;
 #pragma unroll
@@ -292,37 +293,47 @@ __attribute__((amdgpu_waves_per_eu(4, 8))) k_proj_polar(ProjPolarArgs a) {
     const float dct =
         a.dc_dt * a.cart[(size_t)(s / kProjInterleave) * a.cart_stride * kProjInterleave + s % kProjInterleave].x;
 
-    // loads first, branch-free: sample m = |k| of both projections and its
-    // weight; k = M/2 reads m = 0 and is replaced by zero
-    float2 xa[16], xb[16], wk[16];
+    // loads first: samples m = k < M/2 of both projections and their weights.
+    // The thread forms v[k] and, for the thread that owns it, v[M - k] of the
+    // Hermitian extension, which changes hands through LDS (reading sample M - k
+    // and its weight again kept the texture path busy 87 % of the time: 32
+    // slices of 1024^2 121 -> 105 us)
+    float2 xa[8], xb[8], wk[8];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const int k = j + e * T;
-        const int m = k < M / 2 ? k : (k == M / 2 ? 0 : M - k);
+    for (int e = 0; e < 8; ++e) {
+        const int m = j + e * T;
         xa[e] = PA[m];
         xb[e] = PB[m];
         wk[e] = a.kc[m];
     }
     float2 v[16];
+    float2* const xch = lds + fid * M;  // [8][T], before the transform
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const int k = j + e * T;
-        const bool up = k < M / 2;
+    for (int e = 0; e < 8; ++e) {
         float2 ha, hb;
-        if (k == 0) {
+        if (e == 0 && j == 0) {
             // the weight is real at sigma = 0 (phase 1); the origin rule adds dct
             ha = make_float2(wk[e].x * xa[e].x + dct, 0.f);
             hb = make_float2(wk[e].x * xb[e].x + dct, 0.f);
         } else {
             const float2 w = make_float2(0.5f * wk[e].x, -0.5f * wk[e].y);  // conj(weight)/2
-            const float2 ya = cmul(xa[e], w), yb = cmul(xb[e], w);
-            ha = up ? ya : make_float2(ya.x, -ya.y);
-            hb = up ? yb : make_float2(yb.x, -yb.y);
+            ha = cmul(xa[e], w);
+            hb = cmul(xb[e], w);
         }
-        if (k == M / 2 || !va) ha = make_float2(0.f, 0.f);
-        if (k == M / 2 || !vb) hb = make_float2(0.f, 0.f);
+        if (!va) ha = make_float2(0.f, 0.f);
+        if (!vb) hb = make_float2(0.f, 0.f);
         v[e] = make_float2(ha.x - hb.y, ha.y + hb.x);
+        xch[e * T + j] = make_float2(ha.x + hb.y, hb.x - ha.y);  // v[M - k]
     }
+    __syncthreads();
+    // k = j + e T, e >= 8: from sample M - k = (T - j) + (15 - e) T, or for j = 0
+    // (16 - e) T; k = M/2 is zero
+#pragma unroll
+    for (int e = 8; e < 16; ++e) {
+        v[e] = xch[j == 0 ? ((16 - e) & 7) * T : (15 - e) * T + T - j];
+        if (e == 8 && j == 0) v[e] = make_float2(0.f, 0.f);
+    }
+    __syncthreads();  // the transform reuses this LDS
     fft<LOGM, +1>(v, lds, my_off, j, a.tw, my_xm);
 
     const int h = a.n >> 1;
