@@ -126,3 +126,21 @@ def test_angle_search(P, N, angles):
     for b in range(2):
         ref = obst.backproject(sino[b].double().cpu().numpy(), Geometry(N, V, N, angles=th), obst.Params())
         assert_parity(img[b].cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("N,V,P_r,P_c,B,check", [
+    (16, 3, 1, 1, 17, (16,)),        # M = G = 16: one thread per transform, half a projection pair
+    (512, 9, 1, 2, 33, (0, 15, 32)), # G = 1024: a block's columns cross two slice groups, the last ragged
+    (256, 8, 4, 4, 33, (17, 32)),    # the same grid, a quarter of the rows kept
+    (1024, 7, 4, 1, 18, (17,)),      # every row kept
+    (2048, 4, 4, 4, 2, (1,)),        # G = M = 8192: one slice per pass
+])
+def test_projector_column_walk(P, N, V, P_r, P_c, B, check):
+    print(f"[projector] N={N} V={V} Pr={P_r} Pc={P_c} B={B}", flush=True)
+    plan = P.Plan(N, V, pad_radial=P_r, pad_cart=P_c, max_batch=B, adjoint=True)
+    img = _sinos(B, N, N, 77 + N + V)
+    out = plan.project(img)
+    for b in check:
+        assert torch.equal(plan.project(img[b:b + 1].contiguous())[0], out[b])
+        ref = obst.project(img[b].double().cpu().numpy(), Geometry(N, V, N), obst.Params(P_r, P_c))
+        assert_parity(out[b].cpu().numpy(), ref)
