@@ -50,7 +50,7 @@
 // Bound by vector ALU issue: about 90 FP32 operations and one 16-byte table
 // read per point, the reads of a thread's points in flight together. The
 // coordinates of a 2048^2 slice take 20 us of the whole GPU per chunk of
-// slices (34 us with an FP64 square root, FP64 cross products and the library
+// slices where every point's are formed (34 us with an FP64 square root, FP64 cross products and the library
 // arctangent, one point after the other); at N = 4096 and two slices the
 // kernel went from 400 to 315 us, 96 uneven sinograms from 4.9 to 4.3 ms.
 // Per slice, the column is inverse-transformed along b, and only the N rows
@@ -471,7 +471,8 @@ __device__ __forceinline__ void gather_body(const GatherArgs& a, int lblock, int
         // the upper half-plane's rows, and from each its mirror image, which
         // thread T - j (of the same column) takes over through LDS: row b of
         // thread j and point e is row -b of thread T - j and point E - 1 - e
-        // (of thread 0 and point E - e for j = 0)
+        // (of thread 0 and point E - e for j = 0). Half the coordinates: one 256^2
+        // slice 18.4 -> 17.9 us, 96 uneven sinograms 3.48 -> 3.43 ms
         constexpr int H = E / 2;
         static_assert(C::NREG * C::REGION * 2 >= C::WG * H * 3, "the exchange needs LDS");
         unsigned* xch = reinterpret_cast<unsigned*>(lds);
