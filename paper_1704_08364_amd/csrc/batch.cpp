@@ -178,8 +178,9 @@ hipError_t launch_regular(const bst_batch_s* b, const SizeClass& c, void* ws, hi
     ga.uniform = p.uniform ? 1 : 0;
     ga.batch = batch;
     ga.slices_per_block = p.gather_slices;
-    bst::set_radius_scale(ga, p.rscale);
-    ga.vpi_f = (float)p.vpi;
+    ga.radius = bst::radius_scale(p.rscale);
+    ga.vpi_f = bst::split_float(p.vpi).x;
+    ga.vpi_lo = bst::split_float(p.vpi).y;
     ga.ang = p.ang;
     ga.dir = p.dir;
     ga.dc_scale = p.dc_scale;
@@ -242,7 +243,7 @@ hipError_t launch_class(const bst_batch_s* b, const SizeClass& c, void* ws, hipS
     ga.uniform = 1;
     ga.batch = batch;
     ga.slices_per_block = 1;
-    bst::set_radius_scale(ga, p.rscale);
+    ga.radius = bst::radius_scale(p.rscale);
     ga.dc_rule = p.dc_scale * (float)p.V;  // the plan's per-projection factor times its V
     ga.Vs = c.d_V;
     ga.dir = c.d_dir;

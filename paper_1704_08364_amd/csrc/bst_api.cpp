@@ -699,8 +699,9 @@ bst_status run_backproject(bst_plan_t plan, const float* sino, float* img, int32
     ga.zero_slot = plan->M / 2 + plan->lead;
     ga.batch = batch;
     ga.slices_per_block = plan->gather_slices;
-    bst::set_radius_scale(ga, plan->rscale);
-    ga.vpi_f = (float)plan->vpi;
+    ga.radius = bst::radius_scale(plan->rscale);
+    ga.vpi_f = bst::split_float(plan->vpi).x;
+    ga.vpi_lo = bst::split_float(plan->vpi).y;
     ga.ang = plan->ang;
     ga.dir = plan->dir;
     ga.inv_gap = plan->inv_gap;

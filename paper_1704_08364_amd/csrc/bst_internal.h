@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "bst.h"
+#include "gather_point.h"
 
 namespace bst {
 // Host-side trace range (roctx): shows each entry point and pipeline stage as
@@ -130,13 +131,6 @@ struct PolarTiles {
         return (size_t)j * (size_t)S + (size_t)slot;
     }
 };
-// (cos, sin) of an angle for the gather's FP32 cross products: each as a high
-// part of 11 fractional bits, whose products with integers up to 2^12 are exact
-// in FP32, and the rest.
-inline float4 split_direction(double c, double s) {
-    const double ch = std::nearbyint(c * 2048.0) / 2048.0, sh = std::nearbyint(s * 2048.0) / 2048.0;
-    return make_float4((float)ch, (float)(c - ch), (float)sh, (float)(s - sh));
-}
 // slices interleaved in the tent rule's radius-major copy
 constexpr int kTentSlices = 8;
 // slices interleaved in the projector's Cartesian spectra (and summed together
@@ -216,10 +210,8 @@ struct GatherArgs {
                              // points with r >= zero_slot read only zeros
     int batch;
     int slices_per_block;    // whole groups; 0: chosen by the launcher
-    int rshift;              // log2(P_r / P_c): radial samples per Cartesian step
-    float rscale_f;          // 2^rshift
-    float rdown_f;           // 4^min(rshift, 0)
-    float vpi_f;             // V / pi
+    RadiusScale radius;      // radial samples per Cartesian step
+    float vpi_f, vpi_lo;     // V / pi as an FP32 pair
     float dc_scale;
     const double2* ang;      // [V] (cos theta_j, sin theta_j), non-uniform angles
     const float4* dir;       // [V] the same as FP32 pairs (split_direction), uniform angles
@@ -250,12 +242,6 @@ inline int angle_buckets(int V) {
     int k = 8;
     while (k < 4 * V) k *= 2;
     return k;
-}
-// the radius scale P_r / P_c, a power of two between 1/4 and 4
-inline void set_radius_scale(GatherArgs& a, double rscale) {
-    a.rshift = std::ilogb(rscale);
-    a.rscale_f = (float)rscale;
-    a.rdown_f = a.rshift < 0 ? (float)(rscale * rscale) : 1.f;
 }
 
 struct TentArgs {            // pre-gather of the wide points of the tent rule

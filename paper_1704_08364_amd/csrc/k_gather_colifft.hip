@@ -37,22 +37,22 @@
 // Each thread keeps the interpolation coordinates of its E points in
 // three registers each and reuses them for every slice of its chunk. They
 // are exact to FP32 rounding although radius and angle indices reach a few
-// thousand:
-//   radius index r = |(a,b)| P_r/P_c: with m = floor(r) corrected by exact
-//   integers, its fraction is (r^2 - m^2) / (r + m), whose numerator is an
-//   exact integer (up to a power of four);
+// thousand (gather_point.h):
+//   radius index r = |(a,b)| P_r/P_c: m = floor(r) corrected by exact integers,
+//   its fraction by Newton steps on the integer r^2 - m^2;
 //   angle index: a polynomial arctangent picks the interval [theta_j0,
 //   theta_j0+1), then the offset inside it is the arcsine of the cross product
 //   of the point direction with (cos theta_j0, sin theta_j0), which come from
-//   a table as FP32 pairs whose high parts have 11 fractional bits, so their
-//   products with the point's integers are exact and the fraction carries no
-//   cancellation (non-uniform angles: cross products in FP64).
-// Bound by vector ALU issue: about 90 FP32 operations and one 16-byte table
+//   a table as FP32 pairs; the products' rounding errors are carried along, so
+//   the fraction carries no cancellation (non-uniform angles: cross products in
+//   FP64).
+// Bound by vector ALU issue: about 100 FP32 operations and one 16-byte table
 // read per point, the reads of a thread's points in flight together. The
 // coordinates of a 2048^2 slice take 20 us of the whole GPU per chunk of
-// slices where every point's are formed (34 us with an FP64 square root, FP64 cross products and the library
-// arctangent, one point after the other); at N = 4096 and two slices the
-// kernel went from 400 to 315 us, 96 uneven sinograms from 4.9 to 4.3 ms.
+// slices where every point's are formed (34 us with an FP64 square root, FP64
+// cross products and the library arctangent, one point after the other); at N =
+// 4096 and two slices the kernel went from 400 to 315 us, 96 uneven sinograms
+// from 4.9 to 4.3 ms.
 // Per slice, the column is inverse-transformed along b, and only the N rows
 // that survive the crop are written, to a grid laid out [N/8][GT][8]
 // (complex, GT >= G/2 columns per tile row): the 8 rows of a tile and
@@ -176,11 +176,10 @@ constexpr unsigned kSampleMask = 0x1FFFFFFFu;  // o0 without its flag bits
 constexpr int kSeriesAngles = 16;              // fewer angles: the library arctangent
 
 // Uniform angles of a slice: the plan's table, or (uneven batches, a count per
-// slice) the slice's own: (cos, sin) of j pi / V as (cos hi, cos lo, sin hi,
-// sin lo); V / pi in FP32.
+// slice) the slice's own (split_direction of j pi / V); V / pi as an FP32 pair.
 struct AngleView {
     int V;
-    float vpi_f;
+    float vpi_f, vpi_lo;
     const float4* dir;
 };
 
@@ -237,11 +236,8 @@ __device__ __forceinline__ Stencil point_stencil(int col, int bs, const GatherAr
     Stencil none;
     none.o0 = sample_code<TILED>(a, 0, a.zero_slot);
     none.g = none.w1 = 0.f;
-    // radius: n = |(a,b)|^2 is exact (at most 2^25). In units where r^2 =
-    // 4^k n and m are integers, m = floor(r) follows from an approximate root
-    // corrected by the exact d = r^2 - m^2 (both scaled by 4^-k for k < 0).
     const int n = max(col * col + bs * bs, 1);
-    const int up = a.rshift > 0 ? 2 * a.rshift : 0, down = a.rshift < 0 ? -2 * a.rshift : 0;
+    const int up = a.radius.shift > 0 ? 2 * a.radius.shift : 0, down = a.radius.shift < 0 ? -2 * a.radius.shift : 0;
     bool empty = (col == 0 && bs == 0) ||
                  (n << up) >= (int)(__umul24((unsigned)a.zero_slot, (unsigned)a.zero_slot) << down);
     if constexpr (TENT) {
@@ -254,23 +250,9 @@ __device__ __forceinline__ Stencil point_stencil(int col, int bs, const GatherAr
     // the series variant runs on to the end with every point, so that the
     // table reads of a thread's points overlap
     if (!SERIES && empty) return none;
-    const float nf = (float)n;
-    float rinv = __builtin_amdgcn_rsqf(nf);
-    rinv = fmaf(0.5f * rinv, fmaf(-nf * rinv, rinv, 1.f), rinv);
-    const float r = nf * rinv * a.rscale_f;
-    int m0 = (int)r;
-    int d = (n << up) - (int)(__umul24((unsigned)m0, (unsigned)m0) << down);
-    if (d < 0) {
-        m0 -= 1;
-        d += (2 * m0 + 1) << down;
-    } else if (d >= (2 * m0 + 1) << down) {
-        d -= (2 * m0 + 1) << down;
-        m0 += 1;
-    }
-    const float num = (float)d * a.rdown_f, den = r + (float)m0;
-    const float rc = __builtin_amdgcn_rcpf(den);
-    float g = num * rc;
-    g = fmaf(fmaf(-g, den, num), rc, g);
+    const RadialIndex rad = radial_index(n, __builtin_amdgcn_rsqf((float)n), a.radius);
+    const int m0 = rad.m;
+    const float g = rad.g;
 
     // direction of the point on [0, pi): (x, y) with y >= 0
     const bool lower = bs < 0;
@@ -281,25 +263,16 @@ __device__ __forceinline__ Stencil point_stencil(int col, int bs, const GatherAr
     bool flip0 = false;
     if constexpr (!NU) {
         const float xf = (float)x, yf = (float)y;
-        j0 = guess;
-        // |x|, |y| <= 2^12 and the high parts are multiples of 2^-11 of at
-        // most 1: the first difference is exact, the second's error is 2^-36 r
-        const float cross = fmaf(yf, cs.x, -(xf * cs.z)) + fmaf(yf, cs.y, -(xf * cs.w));
         if constexpr (SERIES) {
-            // at most 1.1 pi / 16 from theta_j0: the arcsine series to s^9 is
-            // exact to FP32 rounding
-            const float s = cross * rinv, s2 = s * s;
-            float p = fmaf(s2, 0.0303819444f, 0.0446428571f);
-            p = fmaf(s2, p, 0.075f);
-            p = fmaf(s2, p, 0.1666666667f);
-            f = fmaf(s2 * s, p, s) * av.vpi_f;
+            f = angle_offset(xf, yf, cs, rad, av.vpi_f, av.vpi_lo);
         } else {
-            const float dot = fmaf(xf, cs.x, yf * cs.z) + fmaf(xf, cs.y, yf * cs.w);
+            const double c = (double)cs.x + (double)cs.y, sn = (double)cs.z + (double)cs.w;
+            const float cross = (float)((double)y * c - (double)x * sn), dot = (float)((double)x * c + (double)y * sn);
             f = atan2f(cross, dot) * av.vpi_f;
         }
-        const int step = f < 0.f ? (j0 > 0 ? -1 : 0) : (f >= 1.f && j0 < av.V - 1 ? 1 : 0);
-        j0 += step;
-        f = fminf(fmaxf(f - (float)step, 0.f), 1.f);
+        // the interval next to the guessed one, where there is one
+        j0 = min(max(guess + (int)floorf(f), 0), av.V - 1);
+        f = fminf(fmaxf(f - (float)(j0 - guess), 0.f), 1.f);
     } else {
         // theta_j <= theta exactly when the cross product e_j x u is >= 0 (both
         // directions in [0, pi)): binary search for the last such j, between
@@ -451,7 +424,13 @@ __device__ __forceinline__ void gather_body(const GatherArgs& a, int lblock, int
     const int j = threadIdx.x / F;
     const int col = lblock * F + fid;
     const int V = a.Vs ? a.Vs[s_begin] : a.V;  // this chunk's projections
-    const AngleView av{V, a.Vs ? (float)((double)V / M_PI) : a.vpi_f, a.Vs ? a.dir + a.ang_off[s_begin] : a.dir};
+    AngleView av{V, a.vpi_f, a.vpi_lo, a.dir};
+    if (a.Vs) {
+        const double vpi = (double)V / M_PI;
+        av.vpi_f = (float)vpi;
+        av.vpi_lo = (float)(vpi - (double)av.vpi_f);
+        av.dir = a.dir + a.ang_off[s_begin];
+    }
     const float dc_scale = a.Vs ? a.dc_rule / (float)V : a.dc_scale;
     const bool live = col < G / 2;
     const FftTwiddles<LOGG, +1, E, 2> tw(j, a.tw);
