@@ -160,17 +160,23 @@ template <int LOGG>
 static hipError_t launch_row_t(const RowArgs& a0, int batch, hipStream_t st) {
     using C = RowCfg<LOGG>;
     RowArgs a = a0;
-    // one block per slot of the GPU (256 compute units of 16 waves), each walking
-    // an equal share of the batch's groups, so that the reads of all but its
-    // first group hide behind a transform. With shares of whole slices and
+    // as many blocks as the GPU holds (256 compute units of 16 waves), each
+    // walking an equal share of the batch's groups, so that the reads of all but
+    // its first group hide behind a transform. With shares of whole slices and
     // about four blocks per unit, part rounds and unhidden reads took 7 slices
     // of 2048^2 106 us (now 88), 24 of 1024^2 73 (65), 16 with the monopole 73
     // (59), 2 of 4096^2 156 (131); 64 of 2048^2 are unchanged at 0.60 ms (5.4
-    // TB/s, the rate of a copy).
+    // TB/s, the rate of a copy). Past kMost groups a block, whole rounds of equal
+    // shares: 65 slices of 2048^2 600 us (1064 with the share cut to 64 groups and
+    // a second round of four blocks). From G = 4096 on, where a unit holds one
+    // block, 64 groups (112 slices of 2048^2 985 us, with 16 1021); below, where
+    // several share it, more and shorter blocks balance better (256 slices of
+    // 1024^2 590 us with 16, 610 with 64).
     constexpr int kSlots = 256 * 1024 / (C::WG > 64 ? C::WG : 64);
+    constexpr int kMost = C::G >= 4096 ? 64 : 16;
     a.n_items = a.N / (2 * C::F) * batch;  // groups of the batch
-    a.tiles = (a.n_items + kSlots - 1) / kSlots;
-    if (a.tiles > C::MAX_TILES) a.tiles = C::MAX_TILES;
+    const int rounds = (a.n_items + kSlots * kMost - 1) / (kSlots * kMost);
+    a.tiles = (a.n_items + kSlots * rounds - 1) / (kSlots * rounds);
     const dim3 grid((a.n_items + a.tiles - 1) / a.tiles);
     if (a.mono_part) hipLaunchKernelGGL((k_row_c2r<LOGG, true>), grid, dim3(C::WG), 0, st, a);
     else hipLaunchKernelGGL((k_row_c2r<LOGG, false>), grid, dim3(C::WG), 0, st, a);

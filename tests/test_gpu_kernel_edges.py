@@ -81,6 +81,26 @@ def test_row_blocks_across_slices(P, N, V, filt, mono, B):
     assert_parity(img[B - 1].cpu().numpy(), ref)
 
 
+@pytest.mark.parametrize("N,V,B,check", [
+    (512, 9, 35, (0, 17, 34)),        # 2240 groups in threes: a short last block
+    (128, 4, 4100, (0, 2047, 4099)),  # more than a block's most groups: two rounds of shares of 9
+    (2048, 4, 65, (0, 31, 64)),       # the same where a unit holds one block: two rounds of 33
+])
+def test_row_block_shares(P, N, V, B, check):
+    """Shares that do not divide the batch's groups: every slice as when it runs
+    alone, and nothing written past the last image."""
+    print(f"[row shares] N={N} V={V} B={B}", flush=True)
+    plan = P.Plan(N, V, max_batch=B)
+    sino = torch.randn(B, V, N, generator=torch.Generator().manual_seed(N + B)).to(DEV)
+    buf = torch.full((B * N * N + 16 * N,), 7.0, device=DEV)
+    img = plan.backproject(sino, out=buf[:B * N * N].view(B, N, N))
+    for b in check:
+        assert torch.equal(plan.backproject(sino[b:b + 1])[0], img[b]), b
+    assert bool((buf[B * N * N:] == 7.0).all())
+    ref = obst.backproject(sino[check[-1]].double().cpu().numpy(), Geometry(N, V, N), obst.Params())
+    assert_parity(img[check[-1]].cpu().numpy(), ref)
+
+
 @pytest.mark.parametrize("n,V,B,offset", [
     (16, 1 + 1, 1, 0),    # fewer outputs and projections than a tile
     (32, 17, 2, 1),       # one projection past a tile; rows at odd floats
