@@ -327,8 +327,7 @@ struct ProjColArgs {       // grid^T columns -> Cartesian half-plane spectra, in
     const float2* tw;
     int N;
     int batch;
-    int units;             // ceil(batch/16) * G/2 (slice group x column)
-    int per_block;         // units a block walks (set by the launcher)
+    int units;             // blocks: ceil(batch/16) * G/2 (slice group x column)
 };
 struct ProjGatherArgs {    // CSR transposed gather -> polar^T [V][M/2]
     const float2* cart;    // [batch/16][G/2 * G][16]: the spectra of 16 slices interleaved

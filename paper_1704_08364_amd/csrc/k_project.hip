@@ -102,22 +102,22 @@ struct ProjColCfg {
 };
 
 // Column `col`'s rows of slot `slot` of group `grp` as the transform's input:
-// zeros outside the crop (points keep <= e < 16 - keep of every thread, known
-// to be skipped by the whole block) and for slots past the batch.
-template <int LOGG>
-__device__ __forceinline__ void proj_col_load(const ProjColArgs& a, int grp, int col, int slot, int j, int keep,
+// zeros outside the crop (points KEEP <= e < 16 - KEEP of every thread) and for
+// slots past the batch.
+template <int LOGG, int KEEP>
+__device__ __forceinline__ void proj_col_rows(const ProjColArgs& a, int grp, int col, int slot, int j,
                                               float2 (&v)[16]) {
-    using C = ProjColCfg<LOGG>;
-    constexpr int G = C::G, T = C::T;
+    constexpr int G = ProjColCfg<LOGG>::G, T = ProjColCfg<LOGG>::T;
+    constexpr int N = G * KEEP / 8;
     const int s = grp * kProjInterleave + slot;
     const bool live = s < a.batch;
-    const float2* D = a.grid + (size_t)(live ? s : 0) * a.N * (G / 2);
+    const float2* D = a.grid + (size_t)(live ? s : 0) * N * (G / 2);
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
         v[e] = make_float2(0.f, 0.f);
-        if (e < keep || e >= 16 - keep) {
-            const int p = j + e * T + (e < keep ? a.N / 2 : a.N / 2 - G);
-            v[e] = D[BST_IDX(((size_t)(p >> 3) * (G / 2) + col) * 8 + (p & 7), (size_t)a.N * (G / 2), 2)];
+        if (e < KEEP || e >= 16 - KEEP) {
+            const int p = j + e * T + (e < KEEP ? N / 2 : N / 2 - G);
+            v[e] = D[BST_IDX(((size_t)(p >> 3) * (G / 2) + col) * 8 + (p & 7), (size_t)N * (G / 2), 2)];
         }
     }
     if (!live) {
@@ -125,61 +125,71 @@ __device__ __forceinline__ void proj_col_load(const ProjColArgs& a, int grp, int
         for (int e = 0; e < 16; ++e) v[e] = make_float2(0.f, 0.f);
     }
 }
+// The same with the crop at run time: keep = 8, 4 or 2 for P_c = 1, 2, 4. One
+// branch, so that the reads behind it are issued together.
+template <int LOGG>
+__device__ __forceinline__ void proj_col_load(const ProjColArgs& a, int grp, int col, int slot, int j, int keep,
+                                              float2 (&v)[16]) {
+    if (keep == 8) proj_col_rows<LOGG, 8>(a, grp, col, slot, j, v);
+    else if (keep == 4) proj_col_rows<LOGG, 4>(a, grp, col, slot, j, v);
+    else proj_col_rows<LOGG, 2>(a, grp, col, slot, j, v);
+}
 
-// One unit is a Cartesian column a and a group of kProjInterleave slices: its
-// slices are transformed SL at a time, and each result is stored straight into
-// the interleaved layout [group][a * G + b][slot] that the transposed gather
-// reads. Where the group takes two or more rounds, each thread takes two
-// adjacent slots per pass, so the SL threads that hold point b write 2 * SL
-// adjacent slots of one 128-byte line, and the block completes each of its
-// lines within a few passes, so the partial writes meet in L2 (small grids
-// transform the whole group in one round). Blocks, one per compute unit at two
-// waves per SIMD, walk contiguous ranges of units, spread XCD-contiguously
-// (neighbouring columns share the input tiles' lines), and read the next pass's
-// rows before the current one's transforms (32 slices of 1024^2: 314 -> 286
-// us). Slots past the batch are written as zeros.
+// One block per Cartesian column a and group of kProjInterleave slices: the
+// group's slices are transformed SL at a time, and each result is stored
+// straight into the interleaved layout [group][a * G + b][slot] that the
+// transposed gather reads. Where the group takes two or more rounds, each
+// thread takes two adjacent slots per pass, so the SL threads that hold point
+// b write 2 * SL adjacent slots of one 128-byte line, and the block completes
+// each of its lines within a few passes, so the partial writes meet in L2
+// (small grids transform the whole group in one round); the next pass's rows
+// are read before the current one's transforms. Logical blocks are spread
+// XCD-contiguously, so neighbouring columns (which share the input tiles'
+// lines) share an L2. Slots past the batch are written as zeros. Bound by the
+// strided reads, eight rows of a column to a tile: 32 slices of 1024^2 at P_c = 2
+// take 248 us (303 with each slot's rows read just before its transform), 16 of
+// 2048^2 849 (877). Blocks that walk several columns with the reads running on
+// across them lose more to blocks that end at different times: one such block
+// per compute unit 275 us and 968.
 template <int LOGG>
 __global__ void __launch_bounds__(ProjColCfg<LOGG>::WG) k_proj_cols(ProjColArgs a) {
     using C = ProjColCfg<LOGG>;
     constexpr int G = C::G, T = C::T;
     __shared__ float2 lds[C::SL * G];  // one region per slice, the slices' lanes interleaved
-    const int first = xcd_contiguous(blockIdx.x, gridDim.x) * a.per_block;
-    const int last = min(first + a.per_block, a.units);
-    if (first >= last) return;  // whole block, before any barrier
+    const int unit = xcd_contiguous(blockIdx.x, gridDim.x);
+    if (unit >= a.units) return;  // whole block, before any barrier
+    const int grp = unit / (G / 2), col = unit % (G / 2);
     const int fid = threadIdx.x % C::SL;
     const int j0 = threadIdx.x / C::SL;
     const unsigned my_off = (unsigned)(fid * G) * 8u;
     const int xm = region_xor<LOGG, C::SL>(fid);
-    const int keep = 8 * a.N / G;  // 8, 4 or 2 for P_c = 1, 2, 4
+    const int keep = 8 * a.N / G;
     const FftTwiddles<LOGG, -1, 16> tw(j0, a.tw);
-    auto out_of = [&](int unit) { return a.cart8 + (size_t)unit * G * kProjInterleave; };
+    float2* out = a.cart8 + (size_t)unit * G * kProjInterleave;
     if constexpr (C::ROUNDS >= 2) {
         // two rounds per pass: each thread transforms two adjacent slots and
         // stores them as one 16-byte write
-        constexpr int PASSES = C::ROUNDS / 2;
-        auto load = [&](int i, int j, float2 (&va)[16], float2 (&vb)[16]) {
-            const int unit = first + i / PASSES, slot = (i % PASSES) * 2 * C::SL + 2 * fid;
-            proj_col_load<LOGG>(a, unit / (G / 2), unit % (G / 2), slot, j, keep, va);
-            proj_col_load<LOGG>(a, unit / (G / 2), unit % (G / 2), slot + 1, j, keep, vb);
+        auto load = [&](int r, int j, float2 (&va)[16], float2 (&vb)[16]) {
+            proj_col_load<LOGG>(a, grp, col, r * C::SL + 2 * fid, j, keep, va);
+            proj_col_load<LOGG>(a, grp, col, r * C::SL + 2 * fid + 1, j, keep, vb);
         };
         float2 va[16], vb[16];
         load(0, j0, va, vb);
-        const int passes = (last - first) * PASSES;
 #pragma unroll 1
-        for (int i = 0; i < passes; ++i) {
+        for (int r = 0; r < C::ROUNDS; r += 2) {
             // addresses are re-derived each pass from an opaque copy of the
             // thread index rather than held in registers across passes
             int j = j0;
             asm volatile("" : "+v"(j));
             float2 na[16], nb[16];
-            load(min(i + 1, passes - 1), j, na, nb);
+            if (r + 2 < C::ROUNDS) load(r + 2, j, na, nb);
             FftTwiddles<LOGG, -1, 16> twl = tw;
             twl.pin();
             fft<LOGG, -1>(va, lds, my_off, j, twl, xm);
             twl.pin();
             fft<LOGG, -1>(vb, lds, my_off, j, twl, xm);
-            float4* o4 = reinterpret_cast<float4*>(out_of(first + i / PASSES));
-            const int slot = (i % PASSES) * 2 * C::SL + 2 * fid;
+            float4* o4 = reinterpret_cast<float4*>(out);
+            const int slot = r * C::SL + 2 * fid;
 #pragma unroll
             for (int e = 0; e < 16; ++e)
                 o4[BST_IDX(((size_t)(j + e * T) * kProjInterleave + slot) / 2, (size_t)G * kProjInterleave / 2, 1)] =
@@ -191,18 +201,12 @@ __global__ void __launch_bounds__(ProjColCfg<LOGG>::WG) k_proj_cols(ProjColArgs 
             }
         }
     } else {
-#pragma unroll 1
-        for (int unit = first; unit < last; ++unit) {
-            float2 v[16];
-            proj_col_load<LOGG>(a, unit / (G / 2), unit % (G / 2), fid, j0, keep, v);
-            FftTwiddles<LOGG, -1, 16> twl = tw;
-            twl.pin();
-            fft<LOGG, -1>(v, lds, my_off, j0, twl, xm);
-            float2* out = out_of(unit);
+        float2 v[16];
+        proj_col_load<LOGG>(a, grp, col, fid, j0, keep, v);
+        fft<LOGG, -1>(v, lds, my_off, j0, tw, xm);
 #pragma unroll
-            for (int e = 0; e < 16; ++e)
-                out[BST_IDX((size_t)(j0 + e * T) * kProjInterleave + fid, (size_t)G * kProjInterleave, 1)] = v[e];
-        }
+        for (int e = 0; e < 16; ++e)
+            out[BST_IDX((size_t)(j0 + e * T) * kProjInterleave + fid, (size_t)G * kProjInterleave, 1)] = v[e];
     }
 }
 
@@ -377,11 +381,7 @@ template <int LOGG>
 static hipError_t proj_cols_t(const ProjColArgs& a, int batch, hipStream_t st) {
     using C = ProjColCfg<LOGG>;
     (void)batch;
-    ProjColArgs b = a;
-    // one block per compute unit (1024x1024, 32 slices: 286 us; two 315, four 302)
-    constexpr int kBlocks = 256;
-    b.per_block = C::ROUNDS >= 2 ? (a.units + kBlocks - 1) / kBlocks : 1;
-    hipLaunchKernelGGL(k_proj_cols<LOGG>, dim3((a.units + b.per_block - 1) / b.per_block), dim3(C::WG), 0, st, b);
+    hipLaunchKernelGGL(k_proj_cols<LOGG>, dim3(a.units), dim3(C::WG), 0, st, a);
     return hipGetLastError();
 }
 template <int LOGM>
