@@ -82,6 +82,12 @@ constexpr int gather_points(int G) { return G >= 2048 ? 16 : 8; }
 // against 2.03 for 64 slices of 2048^2; 128-thread ones at G = 1024 and 2048
 // gather 1.1 to 1.3 times slower, 512-thread ones up to 1.3 times.)
 constexpr int gather_threads(int G, bool pipe) { return pipe && G >= 4096 ? 512 : (G <= 512 ? 128 : 256); }
+// Threads that add up a slice's origin terms: the ordinary kernels' block, at most
+// 256.
+constexpr int gather_sum_threads(int G) {
+    const int all = G / 2 * (G / gather_points(G)), most = gather_threads(G, false);
+    return all < most ? all : most;
+}
 // arithmetic instructions between two polar reads of the overlapped gather
 // (64 slices of 2048^2: 2.17 ms with 8, 2.06 with 14, 2.04 with 20, 2.07 with 28)
 constexpr int kReadSpacing = 20;
@@ -134,20 +140,27 @@ __device__ __forceinline__ void static_for(F&& f) {
     }
 }
 
-template <int WG>
-__device__ float block_sum(float x, float* red) {
-    // deterministic: fixed-order wave reduction, then a fixed-order sum of wave totals
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+// Sums of Q values over the block, in a fixed order: each wave's lanes, then the
+// waves. red: Q floats per wave.
+template <int WG, int Q>
+__device__ __forceinline__ void block_sums(float (&x)[Q], float* red) {
     constexpr int NW = (WG + 63) / 64;
-    const int w = threadIdx.x >> 6;
-    if ((threadIdx.x & 63) == 0) red[w] = x;
-    __syncthreads();
-    float t = 0.f;
 #pragma unroll
-    for (int i = 0; i < NW; ++i) t += red[i];
+    for (int o = 32; o > 0; o >>= 1) {
+#pragma unroll
+        for (int k = 0; k < Q; ++k) x[k] += __shfl_xor(x[k], o, 64);
+    }
+#pragma unroll
+    for (int k = 0; k < Q; ++k)
+        if ((threadIdx.x & 63) == 0) red[k * NW + (threadIdx.x >> 6)] = x[k];
     __syncthreads();
-    return t;
+#pragma unroll
+    for (int k = 0; k < Q; ++k) {
+        x[k] = 0.f;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) x[k] += red[k * NW + i];
+    }
+    __syncthreads();
 }
 
 // Interpolation stencil of one Cartesian point, fixed for all slices:
@@ -419,7 +432,7 @@ __device__ __forceinline__ void gather_body(const GatherArgs& a, int lblock, int
     constexpr unsigned kSampleBytes = Q * sizeof(float2);
     constexpr bool TILED = Q == 2 && TAPS == 2;  // the 2 x 4 x 2 tiles of PolarTiles
     __shared__ float2 lds[C::NREG * C::REGION];
-    __shared__ float red[(C::WG + 63) / 64];
+    __shared__ float red[Q * ((C::WG + 63) / 64)];
     const int fid = threadIdx.x % F;
     const int j = threadIdx.x / F;
     const int col = lblock * F + fid;
@@ -555,15 +568,38 @@ __device__ __forceinline__ void gather_body(const GatherArgs& a, int lblock, int
         sg = s0;
         P = polar_rsrc(a.polar + (size_t)(s0 / Q) * lay.group_elems(), group_bytes);
         if (lblock == 0) {
+            // sums of the slices' V origin terms by W threads, U terms of each
+            // slice in flight: one after the other they are the longest chain of a
+            // launch (one slice of 256^2 with V = 16384 61 us in all, now 37; 8 222,
+            // now 140). One order of additions for every launch of a G.
+            constexpr int W = gather_sum_threads(G), U = 8;
+            static_assert(W <= C::WG, "a thread per lane of the sum");
+            const float* row[Q];
+            float acc[Q];
 #pragma unroll
             for (int k = 0; k < Q; ++k) {
-                // the same order of additions in every block size
-                constexpr int W = C::WG < 256 ? C::WG : 256;
-                float acc = 0.f;
-                if (s0 + k < s_end && threadIdx.x < W)
-                    for (int i = threadIdx.x; i < V; i += W) acc += a.dc[(size_t)(s0 + k) * a.V + i];
-                dcv[k] = block_sum<C::WG>(acc, red) * dc_scale;
+                row[k] = a.dc + (size_t)min(s0 + k, s_end - 1) * a.V;
+                acc[k] = 0.f;
             }
+            if (threadIdx.x < W) {
+#pragma unroll 1
+                for (int i = threadIdx.x; i < V; i += U * W) {
+                    float t[Q][U];
+#pragma unroll
+                    for (int k = 0; k < Q; ++k) {
+#pragma unroll
+                        for (int u = 0; u < U; ++u) t[k][u] = row[k][min(i + u * W, V - 1)];
+                    }
+#pragma unroll
+                    for (int k = 0; k < Q; ++k) {
+#pragma unroll
+                        for (int u = 0; u < U; ++u) acc[k] += i + u * W < V ? t[k][u] : 0.f;
+                    }
+                }
+            }
+            block_sums<C::WG, Q>(acc, red);
+#pragma unroll
+            for (int k = 0; k < Q; ++k) dcv[k] = acc[k] * dc_scale;
         }
     };
     // The polar reads of point e, then its values. PIPE: slice 0 of a pair into
