@@ -54,8 +54,14 @@ __device__ __forceinline__ void row_body(const RowArgs& a, int t0, int t1) {
     const int xm = region_xor<LOGG, C::F>(fid);
     const int log_groups = __ffs(a.N / (2 * C::F)) - 1;  // row-pair groups per slice, a power of two
     const FftTwiddles<LOGG, +1, 16> tw(j, a.tw);
-    float mamp = 0.f;
-    int mslice = -1;  // the slice mamp belongs to
+    // the amplitude of the monopole added back to slice s
+    auto mono_amp = [&](int s) {
+        const float inv = a.Vs ? a.mono_inv * (float)a.V / (float)a.Vs[s] : a.mono_inv;
+        return monopole_mass(a.mono_part, s, inv) * a.mono_amp;
+    };
+    int mslice = t0 >> log_groups;
+    float mamp = 0.f;  // of slice mslice
+    if constexpr (MONO) mamp = mono_amp(mslice);
 
     // Thread j's slots e < 8 are k = j + e*T < G/2: the block reads every
     // stored column once (all loads first, no branch between them) and puts
@@ -76,8 +82,7 @@ __device__ __forceinline__ void row_body(const RowArgs& a, int t0, int t1) {
         const int s = t >> log_groups;
         if constexpr (MONO) {
             if (s != mslice) {
-                const float inv = a.Vs ? a.mono_inv * (float)a.V / (float)a.Vs[s] : a.mono_inv;
-                mamp = monopole_mass(a.mono_part, s, inv) * a.mono_amp;
+                mamp = mono_amp(s);
                 mslice = s;
             }
         }
@@ -160,23 +165,25 @@ template <int LOGG>
 static hipError_t launch_row_t(const RowArgs& a0, int batch, hipStream_t st) {
     using C = RowCfg<LOGG>;
     RowArgs a = a0;
-    // as many blocks as the GPU holds (256 compute units of 16 waves), each
-    // walking an equal share of the batch's groups, so that the reads of all but
-    // its first group hide behind a transform. With shares of whole slices and
-    // about four blocks per unit, part rounds and unhidden reads took 7 slices
-    // of 2048^2 106 us (now 88), 24 of 1024^2 73 (65), 16 with the monopole 73
-    // (59), 2 of 4096^2 156 (131); 64 of 2048^2 are unchanged at 0.60 ms (5.4
-    // TB/s, the rate of a copy). Past kMost groups a block, whole rounds of equal
-    // shares: 65 slices of 2048^2 600 us (1064 with the share cut to 64 groups and
-    // a second round of four blocks). From G = 4096 on, where a unit holds one
-    // block, 64 groups (112 slices of 2048^2 985 us, with 16 1021); below, where
-    // several share it, more and shorter blocks balance better (256 slices of
-    // 1024^2 590 us with 16, 610 with 64).
-    constexpr int kSlots = 256 * 1024 / (C::WG > 64 ? C::WG : 64);
-    constexpr int kMost = C::G >= 4096 ? 64 : 16;
+    // Equal shares of the batch's groups. From G = 4096 on a compute unit holds one
+    // block: as many blocks as the GPU holds (256 units of 16 waves), so that the
+    // reads of all but a block's first group hide behind a transform. With shares
+    // of whole slices and about four blocks per unit, part rounds and unhidden
+    // reads took 7 slices of 2048^2 106 us (now 88), 2 of 4096^2 156 (131); 64 of
+    // 2048^2 are unchanged at 0.60 ms (5.4 TB/s, the rate of a copy). Past 64
+    // groups a block, whole rounds of equal shares: 65 slices of 2048^2 608 us (1059
+    // with the share cut to 64 groups and a second round of four blocks).
+    // Below, several blocks share a unit and hide each other's reads; four times
+    // as many, of at most four groups, balance better (5 slices of 1024^2 23.9 ->
+    // 20.0 us, 64 of 512^2 47 -> 39, 65 of 2048^2 at P_c = 1 436 -> 414), but at
+    // G = 2048 with the monopole, whose arithmetic hides more (16 slices of 1024^2
+    // 58 us, in short blocks 65).
+    constexpr int kHeld = 256 * 1024 / (C::WG > 64 ? C::WG : 64);
+    const bool one_block = C::G >= 4096 || (C::G == 2048 && a.mono_part);
+    const int slots = one_block ? kHeld : 4 * kHeld, most = one_block ? 64 : 4;
     a.n_items = a.N / (2 * C::F) * batch;  // groups of the batch
-    const int rounds = (a.n_items + kSlots * kMost - 1) / (kSlots * kMost);
-    a.tiles = (a.n_items + kSlots * rounds - 1) / (kSlots * rounds);
+    const int rounds = (a.n_items + slots * most - 1) / (slots * most);
+    a.tiles = (a.n_items + slots * rounds - 1) / (slots * rounds);
     const dim3 grid((a.n_items + a.tiles - 1) / a.tiles);
     if (a.mono_part) hipLaunchKernelGGL((k_row_c2r<LOGG, true>), grid, dim3(C::WG), 0, st, a);
     else hipLaunchKernelGGL((k_row_c2r<LOGG, false>), grid, dim3(C::WG), 0, st, a);

@@ -82,8 +82,9 @@ def test_row_blocks_across_slices(P, N, V, filt, mono, B):
 
 
 @pytest.mark.parametrize("N,V,B,check", [
-    (512, 9, 35, (0, 17, 34)),        # 2240 groups in threes: a short last block
-    (128, 4, 4100, (0, 2047, 4099)),  # more than a block's most groups: two rounds of shares of 9
+    (512, 9, 35, (0, 17, 34)),        # one group a block
+    (512, 9, 130, (0, 65, 129)),      # 8320 groups in threes: a short last block
+    (128, 4, 4100, (0, 2047, 4099)),  # more than a block's most groups: two rounds of shares of three
     (2048, 4, 65, (0, 31, 64)),       # the same where a unit holds one block: two rounds of 33
 ])
 def test_row_block_shares(P, N, V, B, check):
