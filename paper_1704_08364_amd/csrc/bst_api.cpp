@@ -389,24 +389,27 @@ bst_status bst_plan(const bst_params* p, bst_plan_t* out) {
     }
     for (int j = 0; j < V; ++j) theta[j] = p->angles ? p->angles[j] : (double)j * M_PI / (double)V;
     const double ratio = d / pl->dt;
-    std::vector<float4> dir(V);
-    for (int j = 0; j < V; ++j) {
-        ang[j] = make_double2(std::cos(theta[j]), std::sin(theta[j]));
-        dir[j] = bst::split_direction(ang[j].x, ang[j].y);
-    }
+    for (int j = 0; j < V; ++j) ang[j] = make_double2(std::cos(theta[j]), std::sin(theta[j]));
+    // the gather's directions: split for uniform angles, FP64 for the others
+    const size_t n_dir = pl->uniform ? V : 0, n_ang = pl->uniform ? 0 : V;
+    std::vector<float4> dir(n_dir);
+    for (size_t j = 0; j < n_dir; ++j) dir[j] = bst::split_direction(ang[j].x, ang[j].y);
     // 1 / (theta_{j+1} - theta_j) in the period-pi continuation (the last gap wraps to theta_0 + pi)
     for (int j = 0; j < V; ++j) {
         const double next = (j == V - 1) ? theta[0] + M_PI : theta[j + 1];
         inv_gap[j] = (float)(1.0 / (next - theta[j]));
     }
-    // non-uniform angles: how many lie at or below each bucket edge
+    // non-uniform angles: how many lie at or below each bucket edge (both ascend)
     const int buckets = pl->uniform ? 0 : bst::angle_buckets(V);
-    std::vector<int> below(buckets + 1, 0);
-    for (int k = 0; k <= buckets && !pl->uniform; ++k)
-        below[k] = (int)(std::upper_bound(theta.begin(), theta.end(), (double)k * M_PI / (double)buckets) - theta.begin());
+    std::vector<int> below(pl->uniform ? 0 : buckets + 1);
+    for (int k = 0, j = 0; k < (int)below.size(); ++k) {
+        const double edge = (double)k * M_PI / (double)buckets;
+        while (j < V && theta[j] <= edge) ++j;
+        below[k] = j;
+    }
     for (int j = 0; j < V; ++j) {
-        bf_c[j] = std::cos(theta[j]) * ratio;
-        bf_s[j] = std::sin(theta[j]) * ratio;
+        bf_c[j] = ang[j].x * ratio;
+        bf_s[j] = ang[j].y * ratio;
         double w;
         if (pl->uniform) {
             w = M_PI / V;
@@ -446,8 +449,8 @@ bst_status bst_plan(const bst_params* p, bst_plan_t* out) {
     const size_t o_c = off;     off = up(off + V * sizeof(double));
     const size_t o_s = off;     off = up(off + V * sizeof(double));
     const size_t o_w = off;     off = up(off + V * sizeof(float));
-    const size_t o_ang = off;   off = up(off + V * sizeof(double2));
-    const size_t o_dir = off;   off = up(off + V * sizeof(float4));
+    const size_t o_ang = off;   off = up(off + n_ang * sizeof(double2));
+    const size_t o_dir = off;   off = up(off + n_dir * sizeof(float4));
     const size_t o_gap = off;   off = up(off + V * sizeof(float));
     const size_t o_below = off; off = up(off + below.size() * sizeof(int));
     const size_t o_prow = off;  off = up(off + V * sizeof(float));
@@ -464,10 +467,10 @@ bst_status bst_plan(const bst_params* p, bst_plan_t* out) {
     std::memcpy(host.data() + o_c, bf_c.data(), V * sizeof(double));
     std::memcpy(host.data() + o_s, bf_s.data(), V * sizeof(double));
     std::memcpy(host.data() + o_w, bf_w.data(), V * sizeof(float));
-    std::memcpy(host.data() + o_ang, ang.data(), V * sizeof(double2));
-    std::memcpy(host.data() + o_dir, dir.data(), V * sizeof(float4));
+    if (n_ang) std::memcpy(host.data() + o_ang, ang.data(), n_ang * sizeof(double2));
+    if (n_dir) std::memcpy(host.data() + o_dir, dir.data(), n_dir * sizeof(float4));
     std::memcpy(host.data() + o_gap, inv_gap.data(), V * sizeof(float));
-    std::memcpy(host.data() + o_below, below.data(), below.size() * sizeof(int));
+    if (n_ang) std::memcpy(host.data() + o_below, below.data(), below.size() * sizeof(int));
     std::memcpy(host.data() + o_prow, proj_row.data(), V * sizeof(float));
     std::memcpy(host.data() + o_mphi, mono_phi.data(), n * sizeof(float));
     // band-limited ramp of the brute-force comparison (Kak and Slaney): h[0] =
@@ -574,10 +577,10 @@ bst_status bst_plan(const bst_params* p, bst_plan_t* out) {
     pl->bf_c = reinterpret_cast<double*>(base + o_c);
     pl->bf_s = reinterpret_cast<double*>(base + o_s);
     pl->bf_w = reinterpret_cast<float*>(base + o_w);
-    pl->ang = reinterpret_cast<double2*>(base + o_ang);
-    pl->dir = reinterpret_cast<float4*>(base + o_dir);
+    pl->ang = n_ang ? reinterpret_cast<double2*>(base + o_ang) : nullptr;
+    pl->dir = n_dir ? reinterpret_cast<float4*>(base + o_dir) : nullptr;
     pl->inv_gap = reinterpret_cast<float*>(base + o_gap);
-    pl->ang_below = reinterpret_cast<int*>(base + o_below);
+    pl->ang_below = n_ang ? reinterpret_cast<int*>(base + o_below) : nullptr;
     pl->proj_row = reinterpret_cast<float*>(base + o_prow);
     pl->mono_phi = reinterpret_cast<float*>(base + o_mphi);
     pl->ramp_h = reinterpret_cast<double*>(base + o_ramp);

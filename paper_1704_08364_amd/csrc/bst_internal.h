@@ -47,10 +47,10 @@ struct bst_plan_s {
     double* bf_c;        // [V]          cos(theta_j) * d/dt   (brute force)
     double* bf_s;        // [V]          sin(theta_j) * d/dt
     float* bf_w;         // [V]          w_j
-    double2* ang;        // [V]          (cos theta_j, sin theta_j), non-uniform angles' residuals
-    float4* dir;         // [V]          the same as FP32 pairs (split_direction), uniform angles
+    double2* ang;        // [V]          (cos theta_j, sin theta_j), non-uniform angles only
+    float4* dir;         // [V]          the same as FP32 pairs (split_direction), uniform angles only
     float* inv_gap;      // [V]          1 / (theta_{j+1} - theta_j), last gap to theta_0 + pi
-    int* ang_below;      // [K + 1]      angles theta_j <= k pi / K, k = 0 .. K (angle_buckets(V))
+    int* ang_below;      // [K + 1]      angles theta_j <= k pi / K, k = 0 .. K (angle_buckets(V)), non-uniform only
     // adjoint (bst_project): transposed gather as CSR lists per polar sample
     bool adjoint;
     void* adj_block;
