@@ -125,15 +125,18 @@ __global__ void __launch_bounds__(256) k_bruteforce(BfArgs a) {
 //   out[2p]     = h[0] y[2p]     + sum_q E[p - q]     y[2q + 1],
 //   out[2p + 1] = h[0] y[2p + 1] + sum_q E[p - q + 1] y[2q],   E[x] = h[|2x - 1|],
 // which runs on the FP64 matrix units: A = 16 projections x 4 samples, B = 4
-// samples x 16 outputs. Bound by their rate (V n^2 multiply-adds a slice: 27 us
-// for 2 slices of 1024 x 1024 bins; one thread per output, two LDS reads per
-// multiply-add, took 320 us, this 50).
-// A block takes kRampRows projections and kRampOut output pairs, a wave 32 of
-// them in both parities (so that lanes store whole lines); E's window and
+// samples x 16 outputs. Bound by their rate (V n^2 / 2 multiply-adds a slice: 109
+// us for 8 slices of 1024 x 1024 bins; one thread per output, two LDS reads per
+// multiply-add, took 1024 us, this 136).
+// A block takes kRampRows projections and kRampOut output pairs, a wave 16 of
+// them in both parities (so that lanes store whole lines; 32 of them halve the
+// sample reads but double the chain of products: one slice of 256 x 256 bins 9.5
+// us against 7.9, of 1024 x 1024 29.5 against 24.2, 8 of 2048 x 2048 1124 against
+// 1033); E's window and
 // chunks of kRampChunk sample pairs are staged in LDS, samples as doubles with
 // row strides that put a wave's 16 rows x 4 samples on distinct banks. Samples
 // past n / 2 are zero and outputs past it are dropped.
-constexpr int kRampThreads = 256, kRampRows = 16, kRampOut = 128, kRampChunk = 64;
+constexpr int kRampThreads = 256, kRampRows = 16, kRampOut = 64, kRampChunk = 64;
 constexpr int kRampStride = kRampChunk + 2;
 
 __host__ __device__ constexpr int ramp_pad(int n) { return (n / 2 + kRampChunk - 1) / kRampChunk * kRampChunk; }
@@ -164,10 +167,8 @@ __global__ void __launch_bounds__(kRampThreads) k_ramp_filter(RampArgs a) {
             if (q >= half) y[k] = f2{0.f, 0.f};
         }
     };
-    d4 even[2], odd[2];  // outputs p0 + 16 t + lo of both parities, projections hi + 4 r
-#pragma unroll
-    for (int t = 0; t < 2; ++t) even[t] = odd[t] = d4{0.0, 0.0, 0.0, 0.0};
-    const int p0 = wave * 32;  // in the block
+    d4 even = {0.0, 0.0, 0.0, 0.0}, odd = even;  // outputs p0 + lo of both parities, projections hi + 4 r
+    const int p0 = wave * 16;                    // in the block
     load(0);
     for (int q0 = 0; q0 < qpad; q0 += kRampChunk) {
         __syncthreads();  // the previous chunk is used up
@@ -183,25 +184,19 @@ __global__ void __launch_bounds__(kRampThreads) k_ramp_filter(RampArgs a) {
 #pragma unroll 4
         for (int q = 0; q < kRampChunk; q += 4) {
             const double ae = ys[0][lo][q + hi], ao = ys[1][lo][q + hi];
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                even[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(ao, e[16 * t - q], even[t], 0, 0, 0);
-                odd[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(ae, e[16 * t - q + 1], odd[t], 0, 0, 0);
-            }
+            even = __builtin_amdgcn_mfma_f64_16x16x4f64(ao, e[-q], even, 0, 0, 0);
+            odd = __builtin_amdgcn_mfma_f64_16x16x4f64(ae, e[1 - q], odd, 0, 0, 0);
         }
     }
     float* out = a.out + (size_t)blockIdx.z * a.V * a.n;
+    const int p = P0 + p0 + lo;
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        const int p = P0 + p0 + 16 * t + lo;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int j = row0 + hi + 4 * r;
-            if (p < half && j < a.V) {
-                const f2 c = reinterpret_cast<const f2*>(Y + (size_t)j * a.n)[p];
-                reinterpret_cast<f2*>(out + (size_t)j * a.n)[p] =
-                    f2{(float)fma(a.h[0], (double)c.x, even[t][r]), (float)fma(a.h[0], (double)c.y, odd[t][r])};
-            }
+    for (int r = 0; r < 4; ++r) {
+        const int j = row0 + hi + 4 * r;
+        if (p < half && j < a.V) {
+            const f2 c = reinterpret_cast<const f2*>(Y + (size_t)j * a.n)[p];
+            reinterpret_cast<f2*>(out + (size_t)j * a.n)[p] =
+                f2{(float)fma(a.h[0], (double)c.x, even[r]), (float)fma(a.h[0], (double)c.y, odd[r])};
         }
     }
 }
