@@ -60,11 +60,48 @@ def test_gather_chunking_is_bitwise(P, N, V, P_c, interp, B):
     assert_parity(ref[B - 1].cpu().numpy(), o)
 
 
+@pytest.mark.parametrize("kind,N,V,P_c,B", [
+    ("golden", 1024, 70, 2, 5),       # flipped samples below theta_0, pairs, an odd last one
+    ("golden keys", 512, 90, 4, 5),   # single slices
+    ("golden", 2048, 40, 2, 4),       # G = 4096: 512 threads a block
+    ("tent", 1024, 64, 2, 5),         # wide points from each slice's patch
+    ("tent", 2048, 48, 2, 4),
+])
+def test_overlapped_gather_variants(P, kind, N, V, P_c, B):
+    """Blocks that walk several groups with non-uniform angles and with the tent
+    rule: the bits of blocks of one group, and the oracle's values."""
+    print(f"[overlapped] {kind} N={N} V={V} Pc={P_c} B={B}", flush=True)
+    th = np.sort(np.mod(0.05 + np.arange(V) * (np.pi * (np.sqrt(5.0) - 1.0) / 2.0), np.pi)) if "golden" in kind else None
+    kw = {"interp": "keys", "taper": "keys"} if "keys" in kind else {}
+    if kind == "tent":
+        kw["angular"] = "tent"
+    sino = _sinos(B, V, N, 13 + N + V)
+    ref = P.Plan(N, V, angles=th, pad_cart=P_c, max_batch=B, gather_slices=1024, **kw).backproject(sino)
+    one = P.Plan(N, V, angles=th, pad_cart=P_c, max_batch=1, **kw)
+    for b in range(B):
+        assert torch.equal(one.backproject(sino[b:b + 1])[0], ref[b]), b
+    assert torch.equal(P.Plan(N, V, angles=th, pad_cart=P_c, max_batch=B, **kw).backproject(sino), ref)
+    for b in (B - 2, B - 1):
+        o = obst.backproject(sino[b].double().cpu().numpy(), Geometry(N, V, N, angles=th), obst.Params(2, P_c, **kw))
+        assert_parity(ref[b].cpu().numpy(), o)
+
+
+@pytest.mark.parametrize("N,V,P_r,P_c", [(16, 16, 1, 1), (16, 33, 2, 1), (16, 40, 4, 2), (32, 17, 1, 4)])
+def test_point_coordinates_on_small_grids(P, N, V, P_r, P_c):
+    """The half-plane's mirrored coordinates where two to eight threads share a column."""
+    print(f"[small grids] N={N} V={V} Pr={P_r} Pc={P_c}", flush=True)
+    sino = _sinos(2, V, N, 3 + N + V)
+    img = P.Plan(N, V, pad_radial=P_r, pad_cart=P_c, max_batch=2).backproject(sino)
+    for b in range(2):
+        ref = obst.backproject(sino[b].double().cpu().numpy(), Geometry(N, V, N), obst.Params(P_r, P_c))
+        assert_parity(img[b].cpu().numpy(), ref)
+
+
 @pytest.mark.parametrize("N,V,filt,mono,B", [
     (16, 9, "ramp", 0.0, 3),       # one group a block, several slices in flight
     (2048, 33, "ramp", 0.0, 7),    # blocks of seven groups, across slices
     (2048, 33, "none", 0.4, 7),    # the monopole of each slice a block walks
-    (4096, 17, "ramp", 0.0, 3),    # groups of four rows, the last block short
+    (4096, 17, "ramp", 0.0, 3),    # groups of four rows, twelve a block
     (512, 50, "none", 0.4, 33),
 ])
 def test_row_blocks_across_slices(P, N, V, filt, mono, B):
@@ -105,7 +142,7 @@ def test_row_block_shares(P, N, V, B, check):
 @pytest.mark.parametrize("n,V,B,offset", [
     (16, 1 + 1, 1, 0),    # fewer outputs and projections than a tile
     (32, 17, 2, 1),       # one projection past a tile; rows at odd floats
-    (256, 16, 1, 0),      # exactly one tile of projections, one block of outputs
+    (256, 16, 1, 0),      # exactly one tile of projections, two blocks of outputs
     (512, 31, 3, 1),
     (4096, 18, 1, 0),     # the longest row
 ])
@@ -151,7 +188,7 @@ def test_angle_search(P, N, angles):
 
 @pytest.mark.parametrize("N,V,P_r,P_c,B,check", [
     (16, 3, 1, 1, 17, (16,)),        # M = G = 16: one thread per transform, half a projection pair
-    (512, 9, 1, 2, 33, (0, 15, 32)), # G = 1024: a block's columns cross two slice groups, the last ragged
+    (512, 9, 1, 2, 33, (0, 15, 32)), # G = 1024: three slice groups, the last ragged
     (256, 8, 4, 4, 33, (17, 32)),    # the same grid, a quarter of the rows kept
     (1024, 7, 4, 1, 18, (17,)),      # every row kept
     (2048, 4, 4, 4, 2, (1,)),        # G = M = 8192: one slice per pass
