@@ -829,8 +829,14 @@ static hipError_t launch_gather_k(const GatherArgs& a0, hipStream_t st) {
     if (a.slices_per_block == 0) a.slices_per_block = auto_slices<L>(a.batch);
     const int chunks = (a.batch + a.slices_per_block - 1) / a.slices_per_block;
     if constexpr (CAN_PIPE) {
-        // overlapped only where a block has a second group to overlap
-        if (a.slices_per_block > Q && a.batch > Q) {
+        // overlapped where a block has a second group to overlap; and at G = 4096, where
+        // only its 512 threads hold two columns, for polar spectra that do not stay
+        // in the caches, whose lines the two columns share (2 slices of 2048^2 with
+        // 16384 projections 247 -> 207 us, 8192 168 -> 136, 4096 78 -> 82; cubic
+        // taps, one slice: 181 -> 144, 98 -> 87, 73 -> 67, with 2048 56 -> 58)
+        const size_t group = PolarTiles{Q, a.V, a.S}.group_elems() * sizeof(float2);
+        const bool spread = LOGG == 12 && group > (Q == 2 ? (size_t)150000000 : (size_t)60000000);
+        if ((a.slices_per_block > Q && a.batch > Q) || spread) {
             using C = GatherKernelCfg<LOGG, TAPS, true>;
             hipLaunchKernelGGL((k_gather_colifft<LOGG, TAPS, NU, TENT, true>), dim3((C::G / 2 + C::F - 1) / C::F, chunks),
                                dim3(C::WG), 0, st, a);

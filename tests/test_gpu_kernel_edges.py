@@ -86,6 +86,21 @@ def test_overlapped_gather_variants(P, kind, N, V, P_c, B):
         assert_parity(ref[b].cpu().numpy(), o)
 
 
+@pytest.mark.parametrize("V,interp", [(5000, "linear"), (3700, "keys")])
+def test_gather_of_large_spectra_is_bitwise(P, V, interp):
+    """G = 4096 with more projections than the caches hold: one group alone takes
+    the overlapped form's blocks; the bits do not depend on it."""
+    print(f"[large spectra] V={V} {interp}", flush=True)
+    kw = {"interp": "keys", "taper": "keys"} if interp == "keys" else {}
+    N, B = 2048, 3
+    sino = torch.randn(B, V, N, generator=torch.Generator().manual_seed(V)).to(DEV)
+    ref = P.Plan(N, V, max_batch=B, gather_slices=1024, **kw).backproject(sino)
+    one = P.Plan(N, V, max_batch=1, **kw)
+    for b in range(B):
+        assert torch.equal(one.backproject(sino[b:b + 1])[0], ref[b]), b
+    assert torch.equal(P.Plan(N, V, max_batch=B, gather_slices=2, **kw).backproject(sino), ref)
+
+
 @pytest.mark.parametrize("N,V,P_r,P_c", [(16, 16, 1, 1), (16, 33, 2, 1), (16, 40, 4, 2), (32, 17, 1, 4)])
 def test_point_coordinates_on_small_grids(P, N, V, P_r, P_c):
     """The half-plane's mirrored coordinates where two to eight threads share a column."""
