@@ -59,9 +59,6 @@ __device__ __forceinline__ void row_body(const RowArgs& a, int t0, int t1) {
         const float inv = a.Vs ? a.mono_inv * (float)a.V / (float)a.Vs[s] : a.mono_inv;
         return monopole_mass(a.mono_part, s, inv) * a.mono_amp;
     };
-    int mslice = t0 >> log_groups;
-    float mamp = 0.f;  // of slice mslice
-    if constexpr (MONO) mamp = mono_amp(mslice);
 
     // Thread j's slots e < 8 are k = j + e*T < G/2: the block reads every
     // stored column once (all loads first, no branch between them) and puts
@@ -77,6 +74,9 @@ __device__ __forceinline__ void row_body(const RowArgs& a, int t0, int t1) {
     };
     float4 q[8];
     load(t0, q);
+    int mslice = t0 >> log_groups;
+    float mamp = 0.f;  // of slice mslice, formed beside the first reads
+    if constexpr (MONO) mamp = mono_amp(mslice);
 #pragma unroll 1
     for (int t = t0; t < t1; ++t) {
         const int s = t >> log_groups;
