@@ -320,8 +320,9 @@ bst_status bst_batch_workspace_size(bst_batch_t b, size_t* bytes);
 bst_status bst_batch_classes(bst_batch_t b, int32_t* n_classes);
 /* Autotuner: for every size class, on these inputs, time each stage's
  * persistent grid (1, 2, 4 or 8 blocks per compute unit) and the row stage's
- * tiles per work item (1, 2, 4, 8 or 16 eight-row tiles), keep the fastest,
- * and drop any captured graph. Results do not depend on the choice.
+ * tiles per work item (1, 2, 4, 8 or 16 eight-row tiles, no more than a slice
+ * has; one four-row tile past pad_cart * n_out = 4096), keep the fastest, and
+ * drop any captured graph. Results do not depend on the choice.
  * Synchronizes the stream. Outputs are overwritten. */
 bst_status bst_batch_tune(bst_batch_t b, const float* sinos, const int64_t* sino_off, float* imgs,
                           const int64_t* img_off, void* ws, size_t ws_bytes, void* stream);
